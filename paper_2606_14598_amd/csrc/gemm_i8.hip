@@ -17,8 +17,9 @@
 //   * Split-K variants of it: K divided among several workgroups per tile, int32
 //     partials in a workspace, summed (exactly) by splitk_reduce_kernel, which also runs
 //     the epilogue.
-//   * gemm_i8_kernel: register-staged copies, for small tiles and for operands that are
-//     not 16-byte aligned or whose K is not a multiple of 16 (byte loads).
+//   * gemm_i8_kernel: register-staged copies, for small tiles.
+//   * gemm_i8_any_kernel: operands that are not 16-byte aligned or whose K is not a
+//     multiple of 16, in 16-byte loads at the rows' own alignment.
 //   * gemm_i8_skinny_kernel: few tokens (M <= 128). A workgroup streams 16*FNB weight
 //     rows once for all tokens with v_mfma_i32_16x16x64_i8, its wavefronts splitting K,
 //     partial sums reduced in LDS.
@@ -79,27 +80,54 @@ __device__ __forceinline__ void tile_of(int bid, int tiles_m, int tiles_n, int g
     tn = in / gsz;
 }
 
-// 16 bytes of row `row` at byte `k` of a [rows_left, K] panel, zero outside. VEC: one
-// buffer load (K % 16 == 0, 16-byte aligned base). Otherwise byte loads.
-template <bool VEC>
-__device__ __forceinline__ i32x4 load16(__amdgpu_buffer_rsrc_t rsrc, const int8_t *base,
-                                        int row, int rows_left, int64_t k, int64_t K) {
-    if constexpr (VEC) {
-        const int off = (row < rows_left && k < K) ? (int)(row * K + k) : kOOB;
-        return __builtin_bit_cast(i32x4, __builtin_amdgcn_raw_buffer_load_b128(rsrc, off, 0, 0));
-    } else {
-        uint32_t w[4] = {0, 0, 0, 0};
-        if (row < rows_left) {
-            const int8_t *p = base + (int64_t)row * K;
-#pragma unroll
-            for (int b = 0; b < 16; ++b) {
-                if (k + b < K)
-                    w[b >> 2] |= ((uint32_t)(uint8_t)p[k + b]) << ((b & 3) * 8);
-            }
+// 16 bytes of row `row` at byte `k` of a [rows_left, K] panel (K % 16 == 0, 16-byte
+// aligned base), zero outside.
+__device__ __forceinline__ i32x4 load16(__amdgpu_buffer_rsrc_t rsrc, int row, int rows_left,
+                                        int64_t k, int64_t K) {
+    const int off = (row < rows_left && k < K) ? (int)(row * K + k) : kOOB;
+    return __builtin_bit_cast(i32x4, __builtin_amdgcn_raw_buffer_load_b128(rsrc, off, 0, 0));
+}
+
+// 16 bytes at any address, as one global load or store (the hardware takes any alignment).
+struct __attribute__((packed, aligned(1))) Bytes16 {
+    u32x4 v;
+};
+
+__device__ __forceinline__ i32x4 load16_any(const int8_t *p) {
+    return __builtin_bit_cast(i32x4, reinterpret_cast<const Bytes16 *>(p)->v);
+}
+
+// Bytes [k, min(k + 16, K)) of a row of K bytes at any alignment, zeros behind K (and all
+// zeros when k >= K): a chunk that crosses the row's end is read as the row's last 16
+// bytes and shifted down, so nothing outside the row is touched. Rows shorter than 16
+// bytes are read byte by byte.
+__device__ __forceinline__ i32x4 load16_tail(const int8_t *row, int k, int K) {
+    if (k >= K)
+        return i32x4{0, 0, 0, 0};
+    if (k + 16 <= K)
+        return load16_any(row + k);
+    uint64_t lo = 0, hi = 0;
+    if (K >= 16) {
+        const i32x4 v = load16_any(row + K - 16);
+        lo = (uint32_t)v[0] | (uint64_t)(uint32_t)v[1] << 32;
+        hi = (uint32_t)v[2] | (uint64_t)(uint32_t)v[3] << 32;
+        const int sh = (k - (K - 16)) * 8;          // 8 .. 120
+        if (sh < 64) {
+            lo = lo >> sh | hi << (64 - sh);
+            hi = hi >> sh;
+        } else {
+            lo = hi >> (sh - 64);
+            hi = 0;
         }
-        i32x4 v = {(int)w[0], (int)w[1], (int)w[2], (int)w[3]};
-        return v;
+    } else {
+        for (int b = 0; b < 8; ++b) {
+            if (k + b < K)
+                lo |= (uint64_t)(uint8_t)row[k + b] << (8 * b);
+            if (k + 8 + b < K)
+                hi |= (uint64_t)(uint8_t)row[k + 8 + b] << (8 * b);
+        }
     }
+    return i32x4{(int)(uint32_t)lo, (int)(lo >> 32), (int)(uint32_t)hi, (int)(hi >> 32)};
 }
 
 struct KParams {
@@ -188,8 +216,9 @@ __device__ __forceinline__ void store_tile(const i32x16 (&acc)[FN][FM], const KP
     }
 }
 
-// bf16 epilogue through LDS, for outputs whose rows are 16-byte aligned with N % 8 == 0
-// (kp.out_vec == 2). The wavefront converts one 32-token chunk of its tile at a time into
+// bf16 epilogue through LDS. ALIGNED: output rows are 16-byte aligned with N % 8 == 0
+// (kp.out_vec == 2); otherwise the 16-byte stores go out at any alignment and the row's
+// last chunk element by element. The wavefront converts one 32-token chunk of its tile at a time into
 // a private LDS region of 32 rows x (2*WTN + 16) bytes (the pad spreads the 32 rows over
 // the banks), then writes the chunk back to global memory row by row with 16-byte
 // stores, so every store instruction covers whole contiguous row segments. The token
@@ -207,7 +236,7 @@ __device__ __forceinline__ void store_tile(const i32x16 (&acc)[FN][FM], const KP
 // wavefronts per SIMD registers are short and the other wavefronts hide the latencies:
 // each chunk is converted, read back and stored in turn, with the vectors read from LDS.
 // A tile that lies wholly inside the output stores without bounds tests.
-template <int FN, int FM, int NW>
+template <int FN, int FM, int NW, bool ALIGNED>
 __device__ __forceinline__ void store_tile_bf16_lds(const i32x16 (&acc)[FN][FM],
                                                     const KParams &kp, int64_t m_base,
                                                     int64_t n_base, int lane,
@@ -298,24 +327,45 @@ __device__ __forceinline__ void store_tile_bf16_lds(const i32x16 (&acc)[FN][FM],
             const int64_t nn = n_base + ch * 8;
             // Streaming (nontemporal) stores: the output is not read again by this
             // kernel, and lines that bypass the L2's write-back set leave less to flush
-            // when the kernel ends.
-            u32x4 *dst = reinterpret_cast<u32x4 *>(out + mm * N + nn);
-            if (full) {
+            // when the kernel ends. Rows that are not 16-byte aligned share lines between
+            // neighbouring stores, which the L2 has to merge: plain stores there.
+            uint16_t *dst = out + mm * N + nn;
+            if constexpr (ALIGNED) {
+                if (full) {
 #pragma unroll
-                for (int s = 0; s < NQ; ++s)
-                    if (live(s))
-                        __builtin_nontemporal_store(v[s], dst + (int64_t)s * RPQ * N / 8);
+                    for (int s = 0; s < NQ; ++s)
+                        if (live(s))
+                            __builtin_nontemporal_store(
+                                v[s], reinterpret_cast<u32x4 *>(dst + (int64_t)s * RPQ * N));
+                } else {
+#pragma unroll
+                    for (int s = 0; s < NQ; ++s)
+                        if (live(s) && mm + RPQ * s < M && nn < N)
+                            __builtin_nontemporal_store(
+                                v[s], reinterpret_cast<u32x4 *>(dst + (int64_t)s * RPQ * N));
+                }
             } else {
 #pragma unroll
-                for (int s = 0; s < NQ; ++s)
-                    if (live(s) && mm + RPQ * s < M && nn < N)
-                        __builtin_nontemporal_store(v[s], dst + (int64_t)s * RPQ * N / 8);
+                for (int s = 0; s < NQ; ++s) {
+                    uint16_t *o = dst + (int64_t)s * RPQ * N;
+                    if (!live(s) || mm + RPQ * s >= M || nn >= N)
+                        continue;
+                    if (nn + 8 <= N) {
+                        reinterpret_cast<Bytes16 *>(o)->v = v[s];
+                    } else {
+                        const uint32_t w[4] = {v[s].x, v[s].y, v[s].z, v[s].w};
+#pragma unroll
+                        for (int e = 0; e < 7; ++e)
+                            if (nn + e < N)
+                                o[e] = (uint16_t)((e & 1) ? w[e >> 1] >> 16 : w[e >> 1]);
+                    }
+                }
             }
         }(), ...);
     }(std::make_integer_sequence<int, FM>{});
 }
 
-template <int TM, int TN, int BK, int WM, int WN, bool VEC, int EPI>
+template <int TM, int TN, int BK, int WM, int WN, int EPI>
 __global__ void __launch_bounds__(WM *WN * 64)
 gemm_i8_kernel(KParams kp) {
     constexpr int NT = WM * WN * 64;
@@ -359,12 +409,12 @@ gemm_i8_kernel(KParams kp) {
 #pragma unroll
         for (int i = 0; i < LW; ++i) {
             const int c = i * NT + tid;
-            rw[i] = load16<VEC>(rw_rsrc, wbase, c / CPR, rows_w, k0 + (c % CPR) * 16, K);
+            rw[i] = load16(rw_rsrc, c / CPR, rows_w, k0 + (c % CPR) * 16, K);
         }
 #pragma unroll
         for (int i = 0; i < LX; ++i) {
             const int c = i * NT + tid;
-            rx[i] = load16<VEC>(rx_rsrc, xbase, c / CPR, rows_x, k0 + (c % CPR) * 16, K);
+            rx[i] = load16(rx_rsrc, c / CPR, rows_x, k0 + (c % CPR) * 16, K);
         }
     };
     auto sstore = [&](int st) {
@@ -442,6 +492,193 @@ __device__ __forceinline__ void barrier_nofence() {
     __builtin_amdgcn_sched_barrier(0);
     __builtin_amdgcn_s_barrier();
     __builtin_amdgcn_sched_barrier(0);
+}
+
+// Operands at any alignment and any K (K % 16 != 0 or unaligned pointers): register-staged
+// copies like gemm_i8_kernel, but every 16-byte chunk is one global load at the row's own
+// alignment. Direct-to-LDS loads need dword-aligned addresses, so they are not used here.
+// Rows past M or N are read as the last row (their results are not stored); only the last
+// panel can reach past K, so only it tests for the row's end (load16_tail). The bf16
+// epilogue goes through LDS with stores at the rows' own alignment. D panels are held or
+// in flight in registers ahead of the two LDS stages.
+//
+// Bound by one panel's serial chain (register to LDS, barrier, fragment reads, MFMAs) and
+// the unaligned loads, each of which touches two cache lines: at 2001 x 1001 x 3001 it
+// takes 20.4 us, at K = 1008 15.0 us. Byte loads, which it replaces, took 129 us at
+// K = 1000 (now 17.0 us, 0.71 POP/s).
+template <int TM, int TN, int WM, int WN, int D, int EPI>
+__global__ void __launch_bounds__(WM *WN * 64)
+gemm_i8_any_kernel(KParams kp) {
+    constexpr int BK = 128;
+    constexpr int NW = WM * WN, NT = NW * 64;
+    constexpr int WTM = TM / WM, WTN = TN / WN;
+    constexpr int FM = WTM / 32, FN = WTN / 32;
+    constexpr int CPR = BK / 16;
+    constexpr int RPP = NT / CPR;              // rows covered by one load of every thread
+    constexpr int LW = TN / RPP, LX = TM / RPP;
+    constexpr int STAGE = (TN + TM) * BK;
+    static_assert(FM >= 1 && FN >= 1 && WTM % 32 == 0 && WTN % 32 == 0, "wave tile");
+    static_assert(TN % RPP == 0 && TM % RPP == 0, "load split");
+    static_assert(NW * 32 * (2 * WTN + 16) + (TM + 2 * TN) * 4 <= 2 * STAGE, "epilogue");
+    __shared__ __attribute__((aligned(16))) int8_t smem[2 * STAGE];
+
+    const GemmArgs &a = kp.a;
+    const int tid = threadIdx.x;
+    const int lane = tid & 63, wave = tid >> 6;
+    const int wm = wave % WM, wn = wave / WM;
+    int tm, tn;
+    tile_of(blockIdx.x, kp.tiles_m, kp.tiles_n, kp.gm, tm, tn);
+    const int64_t m0 = (int64_t)tm * TM, n0 = (int64_t)tn * TN;
+    const int64_t M = a.M, N = a.N;
+    const int K = (int)a.K;
+    const int rows_w = (int)((N - n0) < TN ? (N - n0) : TN);
+    const int rows_x = (int)((M - m0) < TM ? (M - m0) : TM);
+    const int8_t *wbase = a.wq + n0 * K;
+    const int8_t *xbase = a.xq + m0 * K;
+
+    i32x16 acc[FN][FM];
+#pragma unroll
+    for (int i = 0; i < FN; ++i)
+#pragma unroll
+        for (int j = 0; j < FM; ++j)
+            acc[i][j] = i32x16{};
+
+    // Thread t copies chunk t % CPR of rows t / CPR + RPP * i.
+    const int kc = tid % CPR, r0 = tid / CPR;
+    int wofs[LW], xofs[LX];                    // row offsets (TN * K < 2^31)
+#pragma unroll
+    for (int i = 0; i < LW; ++i)
+        wofs[i] = min(r0 + RPP * i, rows_w - 1) * K;
+#pragma unroll
+    for (int i = 0; i < LX; ++i)
+        xofs[i] = min(r0 + RPP * i, rows_x - 1) * K;
+    // Panel 0 is the ragged end of K when there is one (integer sums: any order of K gives
+    // the same bits), so the main loop loads whole panels only, without branches that
+    // would make its waits drain the loads in flight. Loads past the last panel repeat it.
+    const int nfull = K / BK, tail = K % BK != 0 ? 1 : 0;
+    i32x4 rw[D][LW], rx[D][LX];
+    auto gload_tail = [&]() __attribute__((always_inline)) {
+#pragma unroll
+        for (int i = 0; i < LW; ++i)
+            rw[0][i] = load16_tail(wbase + wofs[i], nfull * BK + kc * 16, K);
+#pragma unroll
+        for (int i = 0; i < LX; ++i)
+            rx[0][i] = load16_tail(xbase + xofs[i], nfull * BK + kc * 16, K);
+    };
+    auto gload = [&](auto dc, int kt) __attribute__((always_inline)) {
+        constexpr int d = decltype(dc)::value;
+        const int k0 = min(kt - tail, nfull - 1) * BK;
+#pragma unroll
+        for (int i = 0; i < LW; ++i)
+            rw[d][i] = load16_any(wbase + k0 + (uint32_t)(wofs[i] + kc * 16));
+#pragma unroll
+        for (int i = 0; i < LX; ++i)
+            rx[d][i] = load16_any(xbase + k0 + (uint32_t)(xofs[i] + kc * 16));
+    };
+    auto sstore = [&](auto dc, int st) __attribute__((always_inline)) {
+        constexpr int d = decltype(dc)::value;
+        int8_t *sw_ = smem + st * STAGE;
+        int8_t *sx_ = sw_ + TN * BK;
+#pragma unroll
+        for (int i = 0; i < LW; ++i) {
+            const int row = r0 + RPP * i;
+            *reinterpret_cast<i32x4 *>(sw_ + row * BK + ((kc ^ swz<BK>(row)) << 4)) = rw[d][i];
+        }
+#pragma unroll
+        for (int i = 0; i < LX; ++i) {
+            const int row = r0 + RPP * i;
+            *reinterpret_cast<i32x4 *>(sx_ + row * BK + ((kc ^ swz<BK>(row)) << 4)) = rx[d][i];
+        }
+    };
+    auto compute = [&](int st) __attribute__((always_inline)) {
+        const int8_t *sw_ = smem + st * STAGE;
+        const int8_t *sx_ = sw_ + TN * BK;
+#pragma unroll
+        for (int ks = 0; ks < BK / 32; ++ks) {
+            const int ch = ks * 2 + (lane >> 5);
+            i32x4 fa[FN], fb[FM];
+#pragma unroll
+            for (int i = 0; i < FN; ++i) {
+                const int row = wn * WTN + i * 32 + (lane & 31);
+                fa[i] = *reinterpret_cast<const i32x4 *>(sw_ + row * BK + ((ch ^ swz<BK>(row)) << 4));
+            }
+#pragma unroll
+            for (int j = 0; j < FM; ++j) {
+                const int row = wm * WTM + j * 32 + (lane & 31);
+                fb[j] = *reinterpret_cast<const i32x4 *>(sx_ + row * BK + ((ch ^ swz<BK>(row)) << 4));
+            }
+#pragma unroll
+            for (int i = 0; i < FN; ++i)
+#pragma unroll
+                for (int j = 0; j < FM; ++j)
+                    acc[i][j] = __builtin_amdgcn_mfma_i32_32x32x32_i8(fa[i], fb[j], acc[i][j], 0, 0, 0);
+        }
+    };
+
+    // Stores of this wavefront to LDS are done, then every wavefront's; loads into
+    // registers stay in flight.
+    auto sync = [&]() {
+        __builtin_amdgcn_s_waitcnt(0xC07F);   // lgkmcnt(0)
+        barrier_nofence();
+    };
+    const int nk = nfull + tail;
+    using Zero = std::integral_constant<int, 0>;
+    if (nk > 0) {
+        if (tail)
+            gload_tail();
+        else
+            gload(Zero{}, 0);
+        sstore(Zero{}, 0);
+        if (nfull > 0) {
+            // Set d % D holds panel d from here on: panels 1 .. D.
+            [&]<int... d>(std::integer_sequence<int, d...>) {
+                (gload(std::integral_constant<int, (d + 1) % D>{}, d + 1), ...);
+            }(std::make_integer_sequence<int, D>{});
+        }
+        sync();
+        // Panel kt: store panel kt + 1 to the other stage, request panel kt + 1 + D.
+        auto step = [&](auto dc, int kt) __attribute__((always_inline)) {
+            using Next = std::integral_constant<int, (decltype(dc)::value + 1) % D>;
+            const int st = kt & 1;
+            sstore(Next{}, st ^ 1);
+            gload(Next{}, kt + 1 + D);
+            compute(st);
+            sync();
+        };
+        int kt = 0;
+        for (; kt + D < nk; kt += D)
+            [&]<int... d>(std::integer_sequence<int, d...>) {
+                (step(std::integral_constant<int, d>{}, kt + d), ...);
+            }(std::make_integer_sequence<int, D>{});
+        [&]<int... d>(std::integer_sequence<int, d...>) {
+            ([&] {
+                if (kt + d < nk - 1)
+                    step(std::integral_constant<int, d>{}, kt + d);
+            }(), ...);
+        }(std::make_integer_sequence<int, D>{});
+        compute((nk - 1) & 1);
+        sync();
+    }
+    if constexpr (EPI == EPI_BF16) {
+        // The panel stages are free now: the tile's scales and bias behind the staging
+        // regions of the wavefronts.
+        float *const t_sx = reinterpret_cast<float *>(smem + NW * 32 * (2 * WTN + 16));
+        float *const t_sw = t_sx + TM;
+        float *const t_b = t_sw + TN;
+        for (int i = tid; i < TM; i += NT)
+            t_sx[i] = i < rows_x ? a.sx[m0 + i] : 0.0f;
+        for (int i = tid; i < TN; i += NT) {
+            t_sw[i] = i < rows_w ? a.sw[n0 + i] : 0.0f;
+            t_b[i] = (i < rows_w && a.bias) ? __uint_as_float((uint32_t)a.bias[n0 + i] << 16) : 0.0f;
+        }
+        __syncthreads();
+        store_tile_bf16_lds<FN, FM, NW, false>(acc, kp, m0 + wm * WTM, n0 + wn * WTN, lane,
+                                               smem + wave * 32 * (2 * WTN + 16),
+                                               t_sx + wm * WTM, t_sw + wn * WTN,
+                                               t_b + wn * WTN);
+    } else {
+        store_tile<FN, FM, EPI>(acc, kp, m0 + wm * WTM, n0 + wn * WTN, lane);
+    }
 }
 
 // Pipelined variant for 16-byte aligned operands with K % 16 == 0.
@@ -764,15 +1001,19 @@ gemm_i8_lds_kernel(KParams kp) {
     }
     if constexpr (EPI == EPI_BF16) {
         static_assert(NW * 32 * (2 * WTN + 16) <= S * STAGE, "epilogue staging");
-        if (kp.out_vec == 2) {
-            barrier_nofence();   // every wavefront is done reading the panel stages
-            store_tile_bf16_lds<FN, FM, NW>(acc, kp, m0 + wm * WTM, n0 + wn * WTN, lane,
-                                        smem + wave * 32 * (2 * WTN + 16), t_sx + wm * WTM,
-                                        t_sw + wn * WTN, t_b + wn * WTN);
-            return;
-        }
+        barrier_nofence();   // every wavefront is done reading the panel stages
+        int8_t *const region = smem + wave * 32 * (2 * WTN + 16);
+        if (kp.out_vec == 2)
+            store_tile_bf16_lds<FN, FM, NW, true>(acc, kp, m0 + wm * WTM, n0 + wn * WTN, lane,
+                                                  region, t_sx + wm * WTM, t_sw + wn * WTN,
+                                                  t_b + wn * WTN);
+        else
+            store_tile_bf16_lds<FN, FM, NW, false>(acc, kp, m0 + wm * WTM, n0 + wn * WTN, lane,
+                                                   region, t_sx + wm * WTM, t_sw + wn * WTN,
+                                                   t_b + wn * WTN);
+    } else {
+        store_tile<FN, FM, EPI>(acc, kp, m0 + wm * WTM, n0 + wn * WTN, lane);
     }
-    store_tile<FN, FM, EPI>(acc, kp, m0 + wm * WTM, n0 + wn * WTN, lane);
 }
 
 // Weight-streaming kernel for few tokens (M <= 16 * FMB): the product is bound by reading
@@ -793,7 +1034,10 @@ gemm_i8_lds_kernel(KParams kp) {
 // reads the token fragments and the epilogue the scales from there. The linear is then
 // one launch. Each token block is quantized by every channel block that uses it, which
 // the host allows only while those repeated reads of X stay small.
-template <int FMB, int FNB, int NW, int EPI, bool QX = false>
+//
+// ANY: operands at any alignment and any K. Rows past M or N are read as the last row
+// (their results are not stored), the bytes past K of the last super-step as zeros.
+template <int FMB, int FNB, int NW, int EPI, bool QX = false, bool ANY = false>
 __global__ void __launch_bounds__(NW * 64)
 gemm_i8_skinny_kernel(KParams kp) {
     const GemmArgs &a = kp.a;
@@ -845,15 +1089,21 @@ gemm_i8_skinny_kernel(KParams kp) {
     const int nss = (K + 255) / 256;
     for (int j = wave; j < nss; j += NW) {
         const int kb = j * 256 + g * 16;
+        const bool whole = j * 256 + 256 <= K;   // wave-uniform
         i32x4 wv[FNB][4];
 #pragma unroll
         for (int c = 0; c < FNB; ++c)
 #pragma unroll
             for (int s = 0; s < 4; ++s) {
                 const int k = kb + s * 64, row = c * 16 + r;
-                const int off = (k < K && row < rows_w) ? row * K + k : kOOB;
-                wv[c][s] = __builtin_bit_cast(
-                    i32x4, __builtin_amdgcn_raw_buffer_load_b128(rw, off, 0, 0));
+                if constexpr (ANY) {
+                    const int8_t *p = a.wq + (n0 + min(row, rows_w - 1)) * K;
+                    wv[c][s] = whole ? load16_any(p + k) : load16_tail(p, k, K);
+                } else {
+                    const int off = (k < K && row < rows_w) ? row * K + k : kOOB;
+                    wv[c][s] = __builtin_bit_cast(
+                        i32x4, __builtin_amdgcn_raw_buffer_load_b128(rw, off, 0, 0));
+                }
             }
 #pragma unroll
         for (int b = 0; b < FMB; ++b) {
@@ -866,6 +1116,9 @@ gemm_i8_skinny_kernel(KParams kp) {
                     xv[s] = (k < K && m < rows_x)
                                 ? *reinterpret_cast<const i32x4 *>(qx_lds + m * QS + k)
                                 : i32x4{0, 0, 0, 0};
+                } else if constexpr (ANY) {
+                    const int8_t *p = a.xq + (mb + min(m, rows_x - 1)) * K;
+                    xv[s] = whole ? load16_any(p + k) : load16_tail(p, k, K);
                 } else {
                     const int off = (k < K && m < rows_x) ? m * K + k : kOOB;
                     xv[s] = __builtin_bit_cast(
@@ -1261,9 +1514,9 @@ struct Tile {
                 hipLaunchKernelGGL((gemm_i8_lds_kernel<TM, TN, BK, WM, WN, S, EPI_I32>), grid, block, 0, s, kp);
         } else {
             if (epi == EPI_BF16)
-                hipLaunchKernelGGL((gemm_i8_kernel<TM, TN, BK, WM, WN, true, EPI_BF16>), grid, block, 0, s, kp);
+                hipLaunchKernelGGL((gemm_i8_kernel<TM, TN, BK, WM, WN, EPI_BF16>), grid, block, 0, s, kp);
             else
-                hipLaunchKernelGGL((gemm_i8_kernel<TM, TN, BK, WM, WN, true, EPI_I32>), grid, block, 0, s, kp);
+                hipLaunchKernelGGL((gemm_i8_kernel<TM, TN, BK, WM, WN, EPI_I32>), grid, block, 0, s, kp);
         }
         return hipGetLastError();
     }
@@ -1336,18 +1589,57 @@ struct WsxTile {
     }
 };
 
-// Unaligned operands or K % 16 != 0: the register-staged kernel with byte loads.
-struct GenericTile {
-    static constexpr int tm = 128, tn = 128;
-    static hipError_t launch(Epilogue epi, const KParams &kp, hipStream_t s) {
-        const dim3 grid((unsigned)(kp.tiles_m * kp.tiles_n)), block(256);
-        if (epi == EPI_BF16)
-            hipLaunchKernelGGL((gemm_i8_kernel<128, 128, 128, 2, 2, false, EPI_BF16>), grid, block, 0, s, kp);
-        else
-            hipLaunchKernelGGL((gemm_i8_kernel<128, 128, 128, 2, 2, false, EPI_I32>), grid, block, 0, s, kp);
-        return hipGetLastError();
-    }
-};
+// Unaligned operands or K % 16 != 0.
+template <int TM, int TN, int WM, int WN, int D>
+hipError_t launch_any_tile(Epilogue epi, KParams &kp, hipStream_t s) {
+    kp.tiles_m = (int)((kp.a.M + TM - 1) / TM);
+    kp.tiles_n = (int)((kp.a.N + TN - 1) / TN);
+    const dim3 grid((unsigned)(kp.tiles_m * kp.tiles_n)), block(WM * WN * 64);
+    if (epi == EPI_BF16)
+        hipLaunchKernelGGL((gemm_i8_any_kernel<TM, TN, WM, WN, D, EPI_BF16>), grid, block, 0, s, kp);
+    else
+        hipLaunchKernelGGL((gemm_i8_any_kernel<TM, TN, WM, WN, D, EPI_I32>), grid, block, 0, s, kp);
+    return hipGetLastError();
+}
+
+template <int FMB>
+hipError_t launch_any_skinny(Epilogue epi, KParams &kp, hipStream_t s) {
+    kp.tiles_m = 1;
+    kp.tiles_n = (int)((kp.a.N + 15) / 16);
+    const dim3 grid((unsigned)kp.tiles_n), block(1024);
+    if (epi == EPI_BF16)
+        hipLaunchKernelGGL((gemm_i8_skinny_kernel<FMB, 1, 16, EPI_BF16, false, true>), grid,
+                           block, 0, s, kp);
+    else
+        hipLaunchKernelGGL((gemm_i8_skinny_kernel<FMB, 1, 16, EPI_I32, false, true>), grid, block,
+                           0, s, kp);
+    return hipGetLastError();
+}
+
+hipError_t launch_any(Epilogue epi, KParams &kp, hipStream_t s) {
+    const int64_t M = kp.a.M, N = kp.a.N, panels = (kp.a.K + 127) / 128;
+    if (M <= 32 && kp.a.K > 0)
+        return M <= 16 ? launch_any_skinny<1>(epi, kp, s) : launch_any_skinny<2>(epi, kp, s);
+    // Up to 32 tokens the weight is streamed by 16 wavefronts per 16 channels, K split
+    // among them: 7.3 us for 1 x 3001 x 4097 against 11.0 on 64 x 64 tiles. Above, rounds
+    // of 256 workgroups times the tile's time for one (us per 128-byte panel and per tile,
+    // measured on launches of one to four rounds): 256 x 256 wins from about 200 tiles
+    // (8000 x 1500 x 1601: 34.0 us against 39.1 on 128 x 128), 64 x 64 where larger tiles
+    // leave CUs idle (300 x 5001 x 3000: 21.2 against 28.9 us on 128 x 64).
+    auto cost = [&](int64_t tm, int64_t tn, double panel_us, double fixed_us) {
+        const int64_t tiles = ((M + tm - 1) / tm) * ((N + tn - 1) / tn);
+        return (double)((tiles + 255) / 256) * ((double)panels * panel_us + fixed_us);
+    };
+    const double c256 = cost(256, 256, 2.2, 8.0), c128 = cost(128, 128, 0.9, 2.6);
+    const double c12864 = cost(128, 64, 0.72, 2.0), c64 = cost(64, 64, 0.48, 1.5);
+    if (c256 <= c128 && c256 <= c12864 && c256 <= c64)
+        return launch_any_tile<256, 256, 2, 4, 1>(epi, kp, s);
+    if (c128 <= c12864 && c128 <= c64)
+        return launch_any_tile<128, 128, 2, 4, 1>(epi, kp, s);
+    if (c12864 <= c64)
+        return launch_any_tile<128, 64, 4, 2, 3>(epi, kp, s);
+    return launch_any_tile<64, 64, 2, 2, 2>(epi, kp, s);
+}
 
 struct TileEntry {
     TileInfo info;
@@ -1616,8 +1908,7 @@ hipError_t launch_linear_small(const uint16_t *x, const int8_t *wq, const float 
 hipError_t launch_gemm(int id, Epilogue epi, bool vec, const GemmArgs &a, void *ws,
                        size_t ws_bytes, hipStream_t stream) {
     const TileEntry &t = kTiles[id];
-    const int tm = vec ? t.info.tm : GenericTile::tm;
-    const int tn = vec ? t.info.tn : GenericTile::tn;
+    const int tm = t.info.tm, tn = t.info.tn;
     KParams kp;
     kp.a = a;
     kp.tiles_m = (int)((a.M + tm - 1) / tm);
@@ -1638,7 +1929,7 @@ hipError_t launch_gemm(int id, Epilogue epi, bool vec, const GemmArgs &a, void *
     kp.part_vec = 0;
     kp.x = nullptr;
     if (!vec)
-        return GenericTile::launch(epi, kp, stream);
+        return launch_any(epi, kp, stream);
     if (t.info.ksplit > 1) {
         int chunk = 0;
         const int splits = split_count(t.info, a.K, &chunk);
