@@ -34,28 +34,32 @@ __device__ __forceinline__ uint32_t wave_max(uint32_t v) {
     return v;
 }
 
-// Code of one element: clamp(rne(v * inv), -127, 127) as a byte. inv is 0 for a zero
-// row, which yields a zero code (never 0 * inf).
+// Codes of four values: clamp(rne(v * inv), -127, 127) as bytes, the first lowest. The
+// product is clamped (the same as clamping its rounding: the bounds are integers) and
+// 1.5 * 2^23 added, which rounds it to the nearest even integer and leaves the code in
+// the sum's low byte; three byte permutations pack four of them. inv is 0 for a zero row,
+// which yields zero codes (never 0 * inf).
+__device__ __forceinline__ uint32_t code4(float v0, float v1, float v2, float v3, float inv) {
+    const auto one = [&](float v) {
+        return __float_as_uint(__builtin_amdgcn_fmed3f(v * inv, -127.0f, 127.0f) + 12582912.0f);
+    };
+    const uint32_t lo = __builtin_amdgcn_perm(one(v1), one(v0), 0x0C0C0400u);
+    const uint32_t hi = __builtin_amdgcn_perm(one(v3), one(v2), 0x0C0C0400u);
+    return __builtin_amdgcn_perm(hi, lo, 0x05040100u);
+}
+
+// Code of one bf16 element.
 __device__ __forceinline__ uint32_t code(uint32_t h, float inv) {
-    float p = bf16_to_f32(h) * inv;
-    float r = __builtin_rintf(p);
-    r = fminf(fmaxf(r, -127.0f), 127.0f);
+    const float r = __builtin_rintf(__builtin_amdgcn_fmed3f(bf16_to_f32(h) * inv, -127.0f, 127.0f));
     return (uint32_t)((int)r) & 0xFFu;
 }
 
 // 8 codes of a 16-byte bf16 vector packed into 8 bytes.
 __device__ __forceinline__ uint2 code8(uint4 d, float inv) {
-    uint32_t w[4] = {d.x, d.y, d.z, d.w};
-    uint32_t c[8];
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        c[2 * i] = code(w[i] & 0xFFFFu, inv);
-        c[2 * i + 1] = code(w[i] >> 16, inv);
-    }
-    uint2 o;
-    o.x = c[0] | (c[1] << 8) | (c[2] << 16) | (c[3] << 24);
-    o.y = c[4] | (c[5] << 8) | (c[6] << 16) | (c[7] << 24);
-    return o;
+    const auto lo = [](uint32_t w) { return __uint_as_float(w << 16); };
+    const auto hi = [](uint32_t w) { return __uint_as_float(w & 0xFFFF0000u); };
+    return make_uint2(code4(lo(d.x), hi(d.x), lo(d.y), hi(d.y), inv),
+                      code4(lo(d.z), hi(d.z), lo(d.w), hi(d.w), inv));
 }
 
 struct RowScale {

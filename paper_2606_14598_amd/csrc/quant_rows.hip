@@ -63,6 +63,74 @@ __device__ __forceinline__ float gelu_f32(float x) {
     return 0.5f * x * (x < 0.0f ? e : 2.0f - e);
 }
 
+// The same factor from a table: the inputs are bf16, so erfc(|x| / sqrt(2)) / 2 takes one
+// value per magnitude. Below 2^-24 it is 1/2 to float32 precision and from 16 up it is 0,
+// so the 28 binades between (128 magnitudes each) and the end cover every input. The
+// entries are computed here at compile time in double: a series up to z = 1.5, the
+// continued fraction of erfc above.
+constexpr int kGeluLo = (127 - 24) << 7, kGeluHi = (127 + 4) << 7;   // bf16 magnitude bits
+constexpr int kGeluN = kGeluHi - kGeluLo + 1;
+
+constexpr double exp_nonpos(double x) {
+    int n = 0;
+    for (; x < -0.01; x *= 0.5)
+        ++n;
+    double s = 1.0, term = 1.0;
+    for (int i = 1; i <= 7; ++i) {
+        term *= x / i;
+        s += term;
+    }
+    for (; n > 0; --n)
+        s *= s;
+    return s;
+}
+
+constexpr double erfc_const(double z) {
+    constexpr double kInvSqrtPi = 0.56418958354775628695;
+    if (z < 1.5) {
+        double sum = z, term = z;
+        for (int n = 1; n < 60 && (term > 1e-19 || term < -1e-19); ++n) {
+            term *= -z * z / n;
+            sum += term / (2 * n + 1);
+        }
+        return 1.0 - 2.0 * kInvSqrtPi * sum;
+    }
+    double f = z;
+    for (int n = 60; n >= 1; --n)
+        f = z + 0.5 * n / f;
+    return exp_nonpos(-z * z) * kInvSqrtPi / f;
+}
+static_assert(erfc_const(1.0) > 0.157299207050 && erfc_const(1.0) < 0.157299207051, "series");
+static_assert(erfc_const(2.0) > 0.004677734981047 && erfc_const(2.0) < 0.004677734981048, "fraction");
+
+struct alignas(16) GeluTable {
+    float h[(kGeluN + 3) / 4 * 4];   // erfc(|x| / sqrt(2)) / 2 at magnitude kGeluLo + i
+};
+
+constexpr GeluTable make_gelu_table() {
+    GeluTable t{};
+    for (int i = 0; i + 1 < kGeluN; ++i) {
+        double x = 1.0 + (i & 127) / 128.0;
+        for (int e = i >> 7; e < 24; ++e)
+            x *= 0.5;
+        for (int e = 24; e < (i >> 7); ++e)
+            x *= 2.0;
+        const double h = 0.5 * erfc_const(x * 0.70710678118654752440);
+        t.h[i] = h < 1e-45 ? 0.0f : (float)h;
+    }
+    return t;   // the last entry (|x| >= 16) is 0
+}
+__device__ const GeluTable kGeluTable = make_gelu_table();
+
+// GELU of a bf16 value given by its bits h (0 .. 0xFFFF): x * Phi(x) with Phi(x) = h(|x|)
+// for x < 0 and 1 - h(|x|) otherwise, the table in LDS.
+__device__ __forceinline__ float gelu_lookup(uint32_t h, const float *table) {
+    const float x = bf16_to_f32(h);
+    const int i = min(max((int)(h & 0x7FFFu), kGeluLo), kGeluHi) - kGeluLo;
+    const float e = table[i];
+    return x * (x < 0.0f ? e : 1.0f - e);
+}
+
 // The value the row rule sees: T(x), times the channel multiplier c when there is one.
 template <int ACT, bool CM>
 __device__ __forceinline__ float transform(float x, float c) {
@@ -110,6 +178,8 @@ quant_rows_reg(const uint16_t *__restrict__ v, int64_t rows, int64_t K,
     const int64_t groups = (rows + RPB - 1) / RPB;
     const bool wide = (K % 16 == 0) && (reinterpret_cast<uintptr_t>(q) % 16 == 0);
     __shared__ uint32_t part[RPB][TPR / 64];
+    constexpr bool GELU = ACT == ACT_GELU;
+    __shared__ __attribute__((aligned(16))) float gelu[GELU ? sizeof(GeluTable) / 4 : 1];
 
     float cmr[CM ? NV : 1][8];
     if constexpr (CM) {
@@ -153,7 +223,9 @@ quant_rows_reg(const uint16_t *__restrict__ v, int64_t rows, int64_t K,
 #pragma unroll
                 for (int e = 0; e < 8; ++e) {
                     const uint32_t h = (e & 1) ? (w[e >> 1] >> 16) : (w[e >> 1] & 0xFFFFu);
-                    f[j][e] = transform<ACT, CM>(bf16_to_f32(h), CM ? cmr[j][e] : 1.0f);
+                    f[j][e] = GELU ? gelu_lookup(h, gelu) : bf16_to_f32(h);
+                    if constexpr (CM)
+                        f[j][e] *= cmr[j][e];
                     fm = fmaxf(fm, __builtin_fabsf(f[j][e]));
                 }
             }
@@ -182,19 +254,16 @@ quant_rows_reg(const uint16_t *__restrict__ v, int64_t rows, int64_t K,
             if constexpr (PLAIN) {
                 o = code8(d[j], rs.inv);
             } else {
-                uint32_t c[8];
-#pragma unroll
-                for (int e = 0; e < 8; ++e)
-                    c[e] = code_f(f[j][e], rs.inv);
-                o.x = c[0] | (c[1] << 8) | (c[2] << 16) | (c[3] << 24);
-                o.y = c[4] | (c[5] << 8) | (c[6] << 16) | (c[7] << 24);
+                o.x = code4(f[j][0], f[j][1], f[j][2], f[j][3], rs.inv);
+                o.y = code4(f[j][4], f[j][5], f[j][6], f[j][7], rs.inv);
             }
             return o;
         };
-        // The paired path for the plain rule, and for transformed rows with two vectors
-        // per thread; with more, transformed rows measured 3-12% slower with it (GELU and
-        // multiplier variants at K = 12288 and 16384) and keep 8-byte stores.
-        constexpr bool PAIRS = PLAIN || NV == 2;
+        // Transformed rows with the multiplier and an even count of four or more vectors
+        // keep 8-byte stores: the swaps push their registers past what hides the loads
+        // (4608 x 16384 with GELU on 512 x 4: 66.5 us paired, 52.2 not; elsewhere pairs
+        // are up to 15% faster, 4110 x 4608 on 256 x 3: 12.5 against 14.7 us).
+        constexpr bool PAIRS = PLAIN || !CM || NV <= 3 || NV % 2 == 1;
         if (PAIRS && wide) {
             // 16-byte streaming stores (K % 16 == 0, q 16-byte aligned), one pair of
             // vectors at a time. Vectors j and j+1 of lane t are j*TPR + t and
@@ -246,6 +315,11 @@ quant_rows_reg(const uint16_t *__restrict__ v, int64_t rows, int64_t K,
     uint4 a[NV], b[NV];
     int64_t grp = blockIdx.x;
     load(a, grp);
+    if constexpr (GELU) {
+        for (int i = threadIdx.x; i < (int)(sizeof(GeluTable) / 16); i += reg_block_threads<TPR>())
+            reinterpret_cast<float4 *>(gelu)[i] = reinterpret_cast<const float4 *>(&kGeluTable)[i];
+        __syncthreads();
+    }
     for (; grp < groups; grp += 2 * (int64_t)gridDim.x) {
         load(b, grp + gridDim.x);
         process(a, grp);
@@ -336,12 +410,8 @@ quant_rows_loop(const uint16_t *__restrict__ v, int64_t rows, int64_t K,
             for (int64_t vi = t; vi < nvec; vi += 256) {
                 float f[8];
                 values8(vi, f);
-                uint32_t c[8];
-#pragma unroll
-                for (int e = 0; e < 8; ++e)
-                    c[e] = code_f(f[e], rs.inv);
-                d2[vi] = make_uint2(c[0] | (c[1] << 8) | (c[2] << 16) | (c[3] << 24),
-                                    c[4] | (c[5] << 8) | (c[6] << 16) | (c[7] << 24));
+                d2[vi] = make_uint2(code4(f[0], f[1], f[2], f[3], rs.inv),
+                                    code4(f[4], f[5], f[6], f[7], rs.inv));
             }
         } else if constexpr (PLAIN) {
             for (int64_t k = t; k < K; k += 256)
@@ -376,68 +446,72 @@ hipError_t launch_rows(const uint16_t *v, int64_t rows, int64_t K, const float *
                      (reinterpret_cast<uintptr_t>(q) % 8 == 0) &&
                      (reinterpret_cast<uintptr_t>(colmul) % 16 == 0);
     const int64_t nvec = K / 8;
-    // Threads per row and vectors per thread past 256 vectors per row, from sweeps of
-    // both over rows x K (HIP-graph replays of the quantizer on its own, the plain rule
-    // and GELU rows). The vector count per thread is the smallest that covers the row,
-    // so few lanes idle (at K = 4608 a 256 x 4 row leaves 44% of them idle: 11-24%
-    // slower than 128 x 5 for the plain rule, 21-28% for GELU rows, which are ALU-bound);
-    // fewer rows spread a row over more threads. Every choice is within 7% of the
-    // sweeps' best on the shapes measured. Transformed rows differ at K <= 4096 (256 x 2
-    // below 4096 rows; from there one wavefront per row up to K = 3584, 3072 without
-    // GELU, and 128 x 4 above), at K <= 8192 from 4096 rows up (256 x 4) and at
-    // K <= 16384 (the 256-thread block beats 1024-thread rows).
-    if (vec && nvec > 256 && nvec <= 2048) {
-        if (nvec <= 512) {
-            // One wavefront per row with exactly the vectors the row needs.
-            auto wave_row = [&]() {
+    // Threads per row and vectors per thread, from sweeps of both over rows x K with the
+    // matrices rotated through HBM. The vector count per thread is the smallest that
+    // covers the row, so few lanes idle (at K = 4608 a 256 x 4 row leaves 44% of them
+    // idle: 11-24% slower than 128 x 5 for the plain rule); fewer rows spread a row over
+    // more threads.
+    if constexpr (PLAIN) {
+        if (vec && nvec > 256 && nvec <= 2048) {
+            if (nvec <= 512) {
+                if (rows < 1024)
+                    return launch_reg<512, 1, ACT, CM>(v, rows, K, colmul, q, scale, s);
+                // One wavefront per row with exactly the vectors the row needs.
                 if (nvec <= 320)
                     return launch_reg<64, 5, ACT, CM>(v, rows, K, colmul, q, scale, s);
                 if (nvec <= 384)
                     return launch_reg<64, 6, ACT, CM>(v, rows, K, colmul, q, scale, s);
+                if (rows < 4096)
+                    return launch_reg<128, 4, ACT, CM>(v, rows, K, colmul, q, scale, s);
                 if (nvec <= 448)
                     return launch_reg<64, 7, ACT, CM>(v, rows, K, colmul, q, scale, s);
                 return launch_reg<64, 8, ACT, CM>(v, rows, K, colmul, q, scale, s);
-            };
-            if constexpr (PLAIN) {
-                if (rows < 1024)
-                    return launch_reg<512, 1, ACT, CM>(v, rows, K, colmul, q, scale, s);
-                if (rows >= 4096 || nvec <= 384)
-                    return wave_row();
-            } else {
-                // Two vectors per thread keep the 16-byte store pairs of transformed
-                // rows (4 vectors measured 5-8% slower with the multiplier below 4096 rows).
-                if (rows < 4096)
-                    return launch_reg<256, 2, ACT, CM>(v, rows, K, colmul, q, scale, s);
-                // Multiplier-only rows are memory-bound: 7 vectors (8-byte stores) measured
-                // 8-9% slower for them than 128 x 4; GELU rows gain up to 8% from it.
-                if (nvec <= (ACT == ACT_GELU ? 448 : 384))
-                    return wave_row();
             }
-            return launch_reg<128, 4, ACT, CM>(v, rows, K, colmul, q, scale, s);
+            if (nvec <= 768 && rows < 1024)
+                return launch_reg<256, 3, ACT, CM>(v, rows, K, colmul, q, scale, s);
+            if (nvec <= 640)
+                return launch_reg<128, 5, ACT, CM>(v, rows, K, colmul, q, scale, s);
+            if (nvec <= 768)
+                return launch_reg<128, 6, ACT, CM>(v, rows, K, colmul, q, scale, s);
+            if (nvec <= 1024)
+                return rows >= 4096 ? launch_reg<128, 8, ACT, CM>(v, rows, K, colmul, q, scale, s)
+                                    : launch_reg<256, 4, ACT, CM>(v, rows, K, colmul, q, scale, s);
+            // Few long rows (K > 8192 below 256 rows): 512 threads per row, 5-9% faster
+            // than the 256-thread block.
+            if (rows < 256)
+                return nvec <= 1536 ? launch_reg<512, 3, ACT, CM>(v, rows, K, colmul, q, scale, s)
+                                    : launch_reg<512, 4, ACT, CM>(v, rows, K, colmul, q, scale, s);
+            if (nvec <= 1536)
+                return launch_reg<256, 6, ACT, CM>(v, rows, K, colmul, q, scale, s);
+            return rows >= 2048 ? launch_reg<1024, 2, ACT, CM>(v, rows, K, colmul, q, scale, s)
+                                : launch_reg<256, 8, ACT, CM>(v, rows, K, colmul, q, scale, s);
         }
-        if (nvec <= 768 && rows < 1024)
-            return launch_reg<256, 3, ACT, CM>(v, rows, K, colmul, q, scale, s);
-        if (nvec <= 640)
-            return launch_reg<128, 5, ACT, CM>(v, rows, K, colmul, q, scale, s);
-        if (nvec <= 768)
-            return launch_reg<128, 6, ACT, CM>(v, rows, K, colmul, q, scale, s);
-        if (nvec <= 1024) {
-            if constexpr (PLAIN)
-                if (rows >= 4096)
-                    return launch_reg<128, 8, ACT, CM>(v, rows, K, colmul, q, scale, s);
-            return launch_reg<256, 4, ACT, CM>(v, rows, K, colmul, q, scale, s);
+    } else {
+        // Transformed rows hold the float32 row too, so more threads with fewer vectors
+        // each pay from K = 4096 up; GELU rows also spread the copy of the table to LDS
+        // over more threads (us, GELU with the multiplier: 4608 x 16384 52.0 on 512 x 4
+        // against 60.0 on 256 x 8, 8192 x 6144 34.8 on 256 x 3 against 41.7 on 128 x 6,
+        // 8192 x 3072 21.2 on 128 x 3 against 24.2 on 64 x 6, 8192 x 2048 13.6 on 128 x 2
+        // against 16.7 on 64 x 4; multiplier alone: 8192 x 8192 36.5 on 512 x 2 against
+        // 38.5 on 256 x 4, 4110 x 4608 12.5 on 256 x 3 against 12.9 on 128 x 5).
+        constexpr bool GELU = ACT == ACT_GELU;
+        if (vec && nvec > 192 && nvec <= 2048 && (nvec > 256 || rows >= 1024)) {
+            if (nvec <= 256)
+                return launch_reg<128, 2, ACT, CM>(v, rows, K, colmul, q, scale, s);
+            if (GELU && nvec <= 384)
+                return launch_reg<128, 3, ACT, CM>(v, rows, K, colmul, q, scale, s);
+            if (nvec <= 512)
+                return launch_reg<256, 2, ACT, CM>(v, rows, K, colmul, q, scale, s);
+            if (nvec <= 768)
+                return launch_reg<256, 3, ACT, CM>(v, rows, K, colmul, q, scale, s);
+            if (nvec <= 1024)
+                return launch_reg<512, 2, ACT, CM>(v, rows, K, colmul, q, scale, s);
+            if (nvec <= 1536)
+                return launch_reg<512, 3, ACT, CM>(v, rows, K, colmul, q, scale, s);
+            if (GELU || rows < 256)
+                return launch_reg<512, 4, ACT, CM>(v, rows, K, colmul, q, scale, s);
+            return launch_reg<256, 8, ACT, CM>(v, rows, K, colmul, q, scale, s);
         }
-        // Few long rows (K > 8192 below 256 rows): 512 threads per row, 5-9% faster
-        // than the 256-thread block.
-        if (rows < 256)
-            return nvec <= 1536 ? launch_reg<512, 3, ACT, CM>(v, rows, K, colmul, q, scale, s)
-                                : launch_reg<512, 4, ACT, CM>(v, rows, K, colmul, q, scale, s);
-        if (nvec <= 1536)
-            return launch_reg<256, 6, ACT, CM>(v, rows, K, colmul, q, scale, s);
-        if constexpr (PLAIN)
-            if (rows >= 2048)
-                return launch_reg<1024, 2, ACT, CM>(v, rows, K, colmul, q, scale, s);
-        return launch_reg<256, 8, ACT, CM>(v, rows, K, colmul, q, scale, s);
     }
     if (vec && K > 0) {
         // K <= 2048: below 1024 rows a row takes 128 or 256 threads with one vector each
@@ -451,8 +525,10 @@ hipError_t launch_rows(const uint16_t *v, int64_t rows, int64_t K, const float *
         if (nvec <= 256) {
             if (rows < 1024)
                 return launch_reg<256, 1, ACT, CM>(v, rows, K, colmul, q, scale, s);
-            return nvec <= 192 ? launch_reg<64, 3, ACT, CM>(v, rows, K, colmul, q, scale, s)
-                               : launch_reg<64, 4, ACT, CM>(v, rows, K, colmul, q, scale, s);
+            if (nvec <= 192)
+                return launch_reg<64, 3, ACT, CM>(v, rows, K, colmul, q, scale, s);
+            if constexpr (PLAIN)
+                return launch_reg<64, 4, ACT, CM>(v, rows, K, colmul, q, scale, s);
         }
         // Long rows (K up to 65536 for the plain rule, e.g. a 53248-wide projection
         // input; 32768 for transformed rows, whose float32 copy of 8 vectors per thread
