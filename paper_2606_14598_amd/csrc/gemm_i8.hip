@@ -88,13 +88,8 @@ __device__ __forceinline__ i32x4 load16(__amdgpu_buffer_rsrc_t rsrc, int row, in
     return __builtin_bit_cast(i32x4, __builtin_amdgcn_raw_buffer_load_b128(rsrc, off, 0, 0));
 }
 
-// 16 bytes at any address, as one global load or store (the hardware takes any alignment).
-struct __attribute__((packed, aligned(1))) Bytes16 {
-    u32x4 v;
-};
-
 __device__ __forceinline__ i32x4 load16_any(const int8_t *p) {
-    return __builtin_bit_cast(i32x4, reinterpret_cast<const Bytes16 *>(p)->v);
+    return __builtin_bit_cast(i32x4, *reinterpret_cast<const Bytes16 *>(p));
 }
 
 // Bytes [k, min(k + 16, K)) of a row of K bytes at any alignment, zeros behind K (and all
@@ -351,7 +346,7 @@ __device__ __forceinline__ void store_tile_bf16_lds(const i32x16 (&acc)[FN][FM],
                     if (!live(s) || mm + RPQ * s >= M || nn >= N)
                         continue;
                     if (nn + 8 <= N) {
-                        reinterpret_cast<Bytes16 *>(o)->v = v[s];
+                        *reinterpret_cast<Bytes16 *>(o) = __builtin_bit_cast(Bytes16, v[s]);
                     } else {
                         const uint32_t w[4] = {v[s].x, v[s].y, v[s].z, v[s].w};
 #pragma unroll

@@ -9,6 +9,16 @@
 #include <stdint.h>
 
 namespace w8a8 {
+
+// 16 and 8 bytes at any address, as one global load or store (the hardware takes any
+// alignment).
+struct __attribute__((packed, aligned(1))) Bytes16 {
+    uint32_t w[4];
+};
+struct __attribute__((packed, aligned(1))) Bytes8 {
+    uint32_t w[2];
+};
+
 namespace qmath {
 
 __device__ __forceinline__ float bf16_to_f32(uint32_t h) {

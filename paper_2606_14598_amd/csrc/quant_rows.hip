@@ -152,6 +152,27 @@ __device__ __forceinline__ uint32_t abs_bits(float v) {
     return __float_as_uint(v) & 0x7FFFFFFFu;
 }
 
+// Elements [8 vi, min(8 vi + 8, K)) of a row of K >= 8 at any alignment, zeros behind K.
+__device__ __forceinline__ uint4 load8_any(const uint16_t *row, int64_t vi, int64_t nwhole,
+                                           int64_t K) {
+    const int64_t at = vi < nwhole ? vi * 8 : K - 8;
+    const Bytes16 b = *reinterpret_cast<const Bytes16 *>(row + at);
+    uint4 d = make_uint4(b.w[0], b.w[1], b.w[2], b.w[3]);
+    if (vi >= nwhole) {
+        const int sh = (int)(vi * 8 - at) * 16;       // 16 .. 112 bits
+        uint64_t lo = d.x | (uint64_t)d.y << 32, hi = d.z | (uint64_t)d.w << 32;
+        if (sh < 64) {
+            lo = lo >> sh | hi << (64 - sh);
+            hi >>= sh;
+        } else {
+            lo = hi >> (sh - 64);
+            hi = 0;
+        }
+        d = make_uint4((uint32_t)lo, (uint32_t)(lo >> 32), (uint32_t)hi, (uint32_t)(hi >> 32));
+    }
+    return d;
+}
+
 // Register-resident path, persistent and software-pipelined: TPR threads per row
 // (64 = one wavefront, up to 1024 = the block), NV 16-byte vectors per thread (K % 8 ==
 // 0, v 16-byte and q 8-byte aligned). Blocks have max(TPR, 256) threads. Row group j of
@@ -162,10 +183,14 @@ __device__ __forceinline__ uint32_t abs_bits(float v) {
 // With a transform (ACT != ACT_NONE or a multiplier), each thread's columns are the
 // same for every row, so its multipliers are loaded once into registers; the
 // transformed row is held as float32 between the maximum and the coding pass.
+//
+// ANY: rows at any alignment and any K >= 8, by the same 16-byte loads and 8-byte stores
+// at the rows' own alignment. The vector that crosses the row's end is read as the row's
+// last 8 elements shifted down, zeros behind, and its codes are stored one by one.
 template <int TPR>
 constexpr int reg_block_threads() { return TPR > 256 ? TPR : 256; }
 
-template <int TPR, int NV, int ACT, bool CM>
+template <int TPR, int NV, int ACT, bool CM, bool ANY = false>
 __global__ void __launch_bounds__(reg_block_threads<TPR>())
 quant_rows_reg(const uint16_t *__restrict__ v, int64_t rows, int64_t K,
                const float *__restrict__ colmul, int8_t *__restrict__ q,
@@ -174,9 +199,10 @@ quant_rows_reg(const uint16_t *__restrict__ v, int64_t rows, int64_t K,
     constexpr int RPB = reg_block_threads<TPR>() / TPR;
     const int t = threadIdx.x % TPR;
     const int sub = threadIdx.x / TPR;
-    const int64_t nvec = K >> 3;
+    const int64_t nvec = (K + 7) >> 3;
+    const int64_t nwhole = K >> 3;             // vectors that lie wholly in the row
     const int64_t groups = (rows + RPB - 1) / RPB;
-    const bool wide = (K % 16 == 0) && (reinterpret_cast<uintptr_t>(q) % 16 == 0);
+    const bool wide = !ANY && (K % 16 == 0) && (reinterpret_cast<uintptr_t>(q) % 16 == 0);
     __shared__ uint32_t part[RPB][TPR / 64];
     constexpr bool GELU = ACT == ACT_GELU;
     __shared__ __attribute__((aligned(16))) float gelu[GELU ? sizeof(GeluTable) / 4 : 1];
@@ -186,6 +212,20 @@ quant_rows_reg(const uint16_t *__restrict__ v, int64_t rows, int64_t K,
 #pragma unroll
         for (int j = 0; j < NV; ++j) {
             const int64_t vi = (int64_t)j * TPR + t;
+            if constexpr (ANY) {
+                if (vi < nwhole) {
+                    const Bytes16 *c = reinterpret_cast<const Bytes16 *>(colmul + vi * 8);
+                    const Bytes16 lo = c[0], hi = c[1];
+#pragma unroll
+                    for (int e = 0; e < 8; ++e)
+                        cmr[j][e] = __uint_as_float(e < 4 ? lo.w[e & 3] : hi.w[e & 3]);
+                } else {
+#pragma unroll
+                    for (int e = 0; e < 8; ++e)
+                        cmr[j][e] = vi * 8 + e < K ? colmul[vi * 8 + e] : 0.0f;
+                }
+                continue;
+            }
             const float4 *c4 = reinterpret_cast<const float4 *>(colmul) + 2 * vi;
             const float4 lo = vi < nvec ? c4[0] : make_float4(0, 0, 0, 0);
             const float4 hi = vi < nvec ? c4[1] : make_float4(0, 0, 0, 0);
@@ -197,14 +237,19 @@ quant_rows_reg(const uint16_t *__restrict__ v, int64_t rows, int64_t K,
     auto load = [&](uint4 (&d)[NV], int64_t grp) {
         const int64_t row = grp * RPB + sub;
         const bool live = grp < groups && row < rows;
-        const uint4 *src = reinterpret_cast<const uint4 *>(v + (live ? row : 0) * K);
+        const uint16_t *base = v + (live ? row : 0) * K;
+        const uint4 *src = reinterpret_cast<const uint4 *>(base);
 #pragma unroll
         for (int j = 0; j < NV; ++j) {
             const int64_t vi = (int64_t)j * TPR + t;
-            if (live && vi < nvec)
-                d[j] = src[vi];
-            else
-                d[j] = make_uint4(0, 0, 0, 0);
+            d[j] = make_uint4(0, 0, 0, 0);
+            if constexpr (ANY) {
+                if (live && vi < nvec)
+                    d[j] = load8_any(base, vi, nwhole, K);
+            } else {
+                if (live && vi < nvec)
+                    d[j] = src[vi];
+            }
         }
     };
     auto process = [&](const uint4 (&d)[NV], int64_t grp) {
@@ -300,6 +345,23 @@ quant_rows_reg(const uint16_t *__restrict__ v, int64_t rows, int64_t K,
                                                     reinterpret_cast<u32x4v *>(dst + vi));
                     else if (vi < nvec)
                         dst[vi] = c;
+                }
+            }
+        } else if constexpr (ANY) {
+#pragma unroll
+            for (int j = 0; j < NV; ++j) {
+                const int64_t vi = (int64_t)j * TPR + t;
+                if (vi >= nvec)
+                    continue;
+                const uint2 c = codes(j);
+                int8_t *o = q + row * K + vi * 8;
+                if (vi < nwhole) {
+                    *reinterpret_cast<Bytes8 *>(o) = Bytes8{{c.x, c.y}};
+                } else {
+#pragma unroll
+                    for (int e = 0; e < 7; ++e)
+                        if (vi * 8 + e < K)
+                            o[e] = (int8_t)((e < 4 ? c.x : c.y) >> (8 * (e & 3)));
                 }
             }
         } else {
@@ -423,7 +485,7 @@ quant_rows_loop(const uint16_t *__restrict__ v, int64_t rows, int64_t K,
     }
 }
 
-template <int TPR, int NV, int ACT, bool CM>
+template <int TPR, int NV, int ACT, bool CM, bool ANY = false>
 hipError_t launch_reg(const uint16_t *v, int64_t rows, int64_t K, const float *colmul,
                       int8_t *q, float *scale, hipStream_t s) {
     constexpr int BS = reg_block_threads<TPR>();
@@ -433,7 +495,7 @@ hipError_t launch_reg(const uint16_t *v, int64_t rows, int64_t K, const float *c
     // prefetch.
     const int64_t max_blocks = 256 * 2048 / BS;
     const int64_t blocks = groups < max_blocks ? groups : max_blocks;
-    hipLaunchKernelGGL((quant_rows_reg<TPR, NV, ACT, CM>), dim3((unsigned)blocks), dim3(BS),
+    hipLaunchKernelGGL((quant_rows_reg<TPR, NV, ACT, CM, ANY>), dim3((unsigned)blocks), dim3(BS),
                        0, s, v, rows, K, colmul, q, scale);
     return hipGetLastError();
 }
@@ -540,6 +602,26 @@ hipError_t launch_rows(const uint16_t *v, int64_t rows, int64_t K, const float *
         if constexpr (PLAIN)
             if (nvec <= 8192)
                 return launch_reg<1024, 8, ACT, CM>(v, rows, K, colmul, q, scale, s);
+    }
+    // Any alignment: a coarser choice of the same mappings (4000 x 4097: 15.0 us, against
+    // 10.5 at K = 4096; 600 x 20001: 12.5 us). The looped kernel below, one element per
+    // load and store, takes 21.2 and 39.7 us there and is left for K < 8 and the longest
+    // rows.
+    if (!vec && K >= 8 && K <= 32768) {
+        const int64_t n = (K + 7) / 8;
+        if (n <= 64)
+            return launch_reg<64, 1, ACT, CM, true>(v, rows, K, colmul, q, scale, s);
+        if (n <= 128)
+            return launch_reg<64, 2, ACT, CM, true>(v, rows, K, colmul, q, scale, s);
+        if (n <= 256)
+            return launch_reg<128, 2, ACT, CM, true>(v, rows, K, colmul, q, scale, s);
+        if (n <= 512)
+            return launch_reg<256, 2, ACT, CM, true>(v, rows, K, colmul, q, scale, s);
+        if (n <= 1024)
+            return launch_reg<512, 2, ACT, CM, true>(v, rows, K, colmul, q, scale, s);
+        if (n <= 2048)
+            return launch_reg<512, 4, ACT, CM, true>(v, rows, K, colmul, q, scale, s);
+        return launch_reg<1024, 4, ACT, CM, true>(v, rows, K, colmul, q, scale, s);
     }
     const unsigned grid = (unsigned)(rows < 65536 ? rows : 65536);
     if (vec)
