@@ -55,7 +55,7 @@ enum {
     W8A8_ERR_SHAPE = 2,       /* a negative size, or M*K / N*K / M*N beyond 2^62 */
     W8A8_ERR_K_OVERFLOW = 3,  /* K > W8A8_MAX_K: 127*127*K would not fit int32 */
     W8A8_ERR_HIP = 4,         /* HIP reported an error for a launch */
-    W8A8_ERR_WORKSPACE = 5,   /* workspace NULL or smaller than the query returns */
+    W8A8_ERR_WORKSPACE = 5,   /* workspace NULL or smaller than the least it runs with */
     W8A8_ERR_ARG = 6,         /* another invalid argument (e.g. unknown tile id) */
     W8A8_ERR_SCRATCH = 7      /* w8a8_linear_noalloc: the problem exceeds its scratch */
 };
@@ -84,6 +84,10 @@ w8a8_status w8a8_gemm(const int8_t *xq, const float *x_scale, const int8_t *wq,
 
 size_t w8a8_gemm_workspace_bytes(int64_t M, int64_t N, int64_t K);
 
+/* With less than that the call still runs, as long as it has this much: it then splits K
+ * less far or not at all, at the speed that leaves. */
+size_t w8a8_gemm_workspace_least_bytes(int64_t M, int64_t N, int64_t K);
+
 /* Workspace of w8a8_gemm_ex with a given tile id (-1: the table's choice). Tiles that
  * split K among several workgroups per output tile keep int32 partial products
  * [splits][M][N] there; the others need none (0). */
@@ -105,13 +109,16 @@ w8a8_status w8a8_linear(const uint16_t *x, const int8_t *wq, const float *w_scal
 
 size_t w8a8_linear_workspace_bytes(int64_t M, int64_t N, int64_t K);
 
+/* The least w8a8_linear and w8a8_linear_ex run with (see w8a8_gemm_workspace_least_bytes). */
+size_t w8a8_linear_workspace_least_bytes(int64_t M, int64_t N, int64_t K);
+
 /* For callers that cannot allocate (code under HIP graph capture, tight serving loops,
  * harnesses that forbid allocation): w8a8_linear_ex without a workspace argument. The
  * workspace lives in a file-scope device array of W8A8_NOALLOC_SCRATCH_BYTES that each
  * device holds from the library's load until the process ends; the call itself allocates
  * nothing (no hipMalloc, no allocating library routine). Its first call on a device
  * looks up that device's array once (hipGetSymbolAddress), so make it outside graph
- * capture. Problems whose w8a8_linear_workspace_bytes(M,N,K) exceeds the array return
+ * capture. Problems whose w8a8_linear_workspace_least_bytes(M,N,K) exceeds the array return
  * W8A8_ERR_SCRATCH before anything is launched (128 MiB holds, e.g., Xq of 4608 tokens
  * at K = 16384). Every call on a device shares that device's array and leaves its
  * contents behind (nothing in it needs to start at zero): calls that overlap on one

@@ -76,7 +76,9 @@ def load_library():
         "w8a8_gemm_workspace_bytes": ([I64, I64, I64], SZ),
         "w8a8_gemm_workspace_bytes_ex": ([I64, I64, I64, INT], SZ),
         "w8a8_linear": ([P, P, P, P, P, I64, I64, I64, P, SZ, P], INT),
+        "w8a8_gemm_workspace_least_bytes": ([I64, I64, I64], SZ),
         "w8a8_linear_workspace_bytes": ([I64, I64, I64], SZ),
+        "w8a8_linear_workspace_least_bytes": ([I64, I64, I64], SZ),
         "w8a8_linear_one_launch": ([I64, I64, I64], INT),
         "w8a8_gemm_acc_i32": ([P, P, P, I64, I64, I64, P], INT),
         "w8a8_gemm_acc_i32_ex": ([P, P, P, I64, I64, I64, INT, P], INT),
@@ -264,18 +266,21 @@ def smooth_factors(x_amax: torch.Tensor, w_amax: torch.Tensor, alpha: float = 0.
     return s, si
 
 
-def _workspace(nbytes: int, device, workspace):
-    if nbytes == 0:
-        return None
+def _workspace(nbytes: int, device, workspace, least=None):
+    """The caller's workspace, which may be smaller than nbytes (the query's answer) down to
+    least() bytes, or a new one of nbytes."""
     if workspace is not None:
+        if nbytes == 0:
+            return None
         if not isinstance(workspace, torch.Tensor) or not workspace.is_contiguous():
             raise ValueError("workspace must be a contiguous torch.Tensor")
         if workspace.device != torch.device(device):
             raise ValueError(f"workspace is on {workspace.device}, expected {device}")
-        if workspace.numel() * workspace.element_size() < nbytes:
-            raise ValueError(f"workspace needs {nbytes} bytes")
+        have = workspace.numel() * workspace.element_size()
+        if have < nbytes and (least is None or have < least()):
+            raise ValueError(f"workspace needs {nbytes if least is None else least()} bytes")
         return workspace
-    return torch.empty(nbytes, dtype=torch.uint8, device=device)
+    return torch.empty(nbytes, dtype=torch.uint8, device=device) if nbytes else None
 
 
 def gemm(xq, x_scale, wq, w_scale, bias=None, *, tile: int = -1, out=None,
@@ -297,7 +302,9 @@ def gemm(xq, x_scale, wq, w_scale, bias=None, *, tile: int = -1, out=None,
         _check_out(out, torch.bfloat16, (M, N), xq.device)
     y = out if out is not None else torch.empty((M, N), dtype=torch.bfloat16,
                                                 device=xq.device)
-    ws = _workspace(gemm_workspace_bytes(M, N, K, tile), xq.device, workspace)
+    ws = _workspace(gemm_workspace_bytes(M, N, K, tile), xq.device, workspace,
+                    (lambda: int(load_library().w8a8_gemm_workspace_least_bytes(M, N, K)))
+                    if tile == -1 else None)
     nws = 0 if ws is None else ws.numel() * ws.element_size()
     with torch.cuda.device(xq.device):
         _call("w8a8_gemm_ex", _ptr(xq), _ptr(x_scale), _ptr(wq), _ptr(w_scale), _ptr(bias),
@@ -332,7 +339,8 @@ def linear(x, wq, w_scale, bias=None, *, act: str = "none", col_mul=None, out=No
                                                 device=x.device)
     if M == 0 or N == 0:
         return y.reshape(*lead, N)
-    ws = _workspace(linear_workspace_bytes(M, N, K), x.device, workspace)
+    ws = _workspace(linear_workspace_bytes(M, N, K), x.device, workspace,
+                    lambda: int(load_library().w8a8_linear_workspace_least_bytes(M, N, K)))
     with torch.cuda.device(x.device):
         _call("w8a8_linear_ex", _ptr(x2), a, _ptr(cm), _ptr(wq), _ptr(w_scale), _ptr(bias),
               _ptr(y), M, N, K, _ptr(ws), ws.numel() * ws.element_size(), _stream(x.device))

@@ -34,6 +34,7 @@
 #include "w8a8_internal.hpp"
 #include "quant_math.hpp"
 
+#include <algorithm>
 #include <atomic>
 #include <utility>
 
@@ -64,13 +65,21 @@ __device__ __forceinline__ int swz(int row) {
         return ((row >> 1) ^ (row >> 3)) & 3;
 }
 
-// Logical tile of workgroup `bid`: XCD-contiguous runs, grouped raster inside.
-__device__ __forceinline__ void tile_of(int bid, int tiles_m, int tiles_n, int gm,
-                                        int &tm, int &tn) {
-    const int total = tiles_m * tiles_n;
+// Logical tile (and K-range) of workgroup `bid`: XCD-contiguous runs, the K-ranges
+// outermost (an XCD then reads few K-ranges of many tiles, and the workgroups that share
+// operand panels run side by side), grouped raster inside.
+__device__ __forceinline__ void tile_of(int bid, int tiles_m, int tiles_n, int gm, int splits,
+                                        int &tm, int &tn, int &split) {
+    const int tiles = tiles_m * tiles_n;
+    const int total = tiles * splits;
     const int xcd = bid & 7, slot = bid >> 3;
     const int q = total >> 3, r = total & 7;
-    const int t = xcd * q + min(xcd, r) + slot;
+    int t = xcd * q + min(xcd, r) + slot;
+    split = 0;
+    if (splits > 1) {
+        split = t / tiles;
+        t -= split * tiles;
+    }
     const int per_group = gm * tiles_n;
     const int g = t / per_group;
     const int first = g * gm;
@@ -378,8 +387,8 @@ gemm_i8_kernel(KParams kp) {
     const int tid = threadIdx.x;
     const int lane = tid & 63, wave = tid >> 6;
     const int wm = wave % WM, wn = wave / WM;
-    int tm, tn;
-    tile_of(blockIdx.x, kp.tiles_m, kp.tiles_n, kp.gm, tm, tn);
+    int tm, tn, split;
+    tile_of(blockIdx.x, kp.tiles_m, kp.tiles_n, kp.gm, 1, tm, tn, split);
     const int64_t m0 = (int64_t)tm * TM, n0 = (int64_t)tn * TN;
     const int64_t M = a.M, N = a.N, K = a.K;
     const int rows_w = (int)((N - n0) < TN ? (N - n0) : TN);
@@ -521,8 +530,8 @@ gemm_i8_any_kernel(KParams kp) {
     const int tid = threadIdx.x;
     const int lane = tid & 63, wave = tid >> 6;
     const int wm = wave % WM, wn = wave / WM;
-    int tm, tn;
-    tile_of(blockIdx.x, kp.tiles_m, kp.tiles_n, kp.gm, tm, tn);
+    int tm, tn, split;
+    tile_of(blockIdx.x, kp.tiles_m, kp.tiles_n, kp.gm, 1, tm, tn, split);
     const int64_t m0 = (int64_t)tm * TM, n0 = (int64_t)tn * TN;
     const int64_t M = a.M, N = a.N;
     const int K = (int)a.K;
@@ -721,15 +730,8 @@ gemm_i8_lds_kernel(KParams kp) {
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int wm = wave % WM, wn = wave / WM;
-    // Split-K: workgroup b works on K-range `split` of tile b mod (tiles_m * tiles_n).
-    int blk = blockIdx.x, split = 0;
-    if (kp.k_split > 1) {
-        const int ntiles = kp.tiles_m * kp.tiles_n;
-        split = blk / ntiles;
-        blk -= split * ntiles;
-    }
-    int tm, tn;
-    tile_of(blk, kp.tiles_m, kp.tiles_n, kp.gm, tm, tn);
+    int tm, tn, split;                                   // split-K: the K-range
+    tile_of(blockIdx.x, kp.tiles_m, kp.tiles_n, kp.gm, kp.k_split, tm, tn, split);
     const int64_t m0 = (int64_t)tm * TM, n0 = (int64_t)tn * TN;
     const int64_t M = a.M, N = a.N;
     const int K = (int)a.K;                              // row stride of Xq and Wq
@@ -1645,7 +1647,7 @@ struct TileEntry {
 #define W8A8_TILE(NAME, TM, TN, BK, WM, WN, GM, S)                                          \
     TileEntry {                                                                              \
         {NAME, TM, TN, BK, Tile<TM, TN, BK, WM, WN, S>::threads,                            \
-         Tile<TM, TN, BK, WM, WN, S>::lds, 1, -1, 0},                                        \
+         Tile<TM, TN, BK, WM, WN, S>::lds, 1, -1, 0, S >= 2},                                        \
             GM, &Tile<TM, TN, BK, WM, WN, S>::launch                                         \
     }
 
@@ -1653,20 +1655,20 @@ struct TileEntry {
 #define W8A8_TILE_SPLIT(NAME, TM, TN, BK, WM, WN, GM, S, KSPLIT, BASE)                    \
     TileEntry {                                                                              \
         {NAME, TM, TN, BK, Tile<TM, TN, BK, WM, WN, S>::threads,                            \
-         Tile<TM, TN, BK, WM, WN, S>::lds, KSPLIT, BASE, 0},                                 \
+         Tile<TM, TN, BK, WM, WN, S>::lds, KSPLIT, BASE, 0, true},                                 \
             GM, &Tile<TM, TN, BK, WM, WN, S>::launch                                         \
     }
 
 #define W8A8_SKINNY(NAME, FMB, FNB, NW)                                                  \
     TileEntry {                                                                              \
         {NAME, 16 * FMB, 16 * FNB, 256, SkinnyTile<FMB, FNB, NW>::threads,                  \
-         SkinnyTile<FMB, FNB, NW>::lds, 1, -1, 1},                                           \
+         SkinnyTile<FMB, FNB, NW>::lds, 1, -1, 1, false},                                           \
             1, &SkinnyTile<FMB, FNB, NW>::launch                                             \
     }
 
 #define W8A8_WSX(NAME, FMB, FNB, NW, D)                                                     \
     TileEntry {                                                                              \
-        {NAME, 16 * FMB, 16 * FNB, 128, WsxTile<FMB, FNB, NW, D>::threads, 0, 1, -1, 2},     \
+        {NAME, 16 * FMB, 16 * FNB, 128, WsxTile<FMB, FNB, NW, D>::threads, 0, 1, -1, 2, false},     \
             1, &WsxTile<FMB, FNB, NW, D>::launch                                             \
     }
 
@@ -1743,11 +1745,42 @@ struct TileCost {
 
 static_assert(sizeof(kTileCost) / sizeof(kTileCost[0]) == kNumTiles, "one cost per tile");
 
-// Shapes without a table entry. Above 128 tokens a wave-quantization cost model picks
-// the tile: a launch of T workgroups on 256 CUs takes ceil(T / 256) rounds, and a round
-// of tile t costs c_t + d_t * K * TM * TN / 1e9 (kTileCost, fitted offline to the
-// sweep). With few tokens, rules from a sweep of the weight-streaming and deep-ring
-// tiles pick it.
+// Cost of a split besides its main launch, in us: a second launch, its reads of each
+// partial, and one write and one read of the partials' bytes.
+constexpr double kSplitFixedUs = 2.0, kSplitUs = 0.25, kSplitUsPerMB = 0.4;
+constexpr uint32_t kMaxSplits = 16;
+constexpr int64_t kSplitWorkspace = 80 << 20;   // bytes of partials at most
+// K is split only where the best unsplit plan takes longer than this: a call's second launch
+// and its larger workspace cost the host some 5 us, which a shorter GEMM does not hide
+// (38 tokens, K = 3648, N = 2752 and 448: 43.9 us with the first one split, 37.7 without).
+constexpr double kSplitWorthUs = 12.0;
+// A table entry, which was timed on its own shape, gives way only to a clear gain.
+constexpr double kOverTable = 0.85;
+
+// The weight-streaming tiles, in us: fixed part, per 1000 of K, per round of 256 workgroups,
+// and per MB of weight rows and of token rows that the workgroups read. Fitted like
+// kTileCost, on the shapes of up to 128 tokens.
+struct StreamCost {
+    int tile;
+    double fixed, k, round, w, x;
+};
+const StreamCost kStreamCost[] = {
+    {15, 3.168, 0.419, 0.602, 0.1546, 0.0000},  // skinny_m16n16w16
+    {16, 3.064, 0.732, 0.671, 0.1872, 0.0148},  // skinny_m32n16w16
+    {17, 1.979, 1.478, 2.020, 0.0019, 0.5314},  // skinny_m16n64w16
+    {18, 1.511, 1.437, 2.594, 0.1029, 0.0544},  // skinny_m64n32w16
+    {19, 0.317, 2.092, 4.337, 0.0757, 0.1143},  // skinny_m128n32w8
+    {36, 3.808, 0.355, 0.603, 0.0001, 0.1572},  // wsx_m16n16w8d4
+    {37, 3.208, 0.723, 1.585, 0.0000, 0.2670},  // wsx_m16n32w8d4
+    {38, 2.324, 1.419, 3.660, 0.0000, 0.5010},  // wsx_m16n64w8d4
+    {39, 3.388, 0.983, 0.916, 0.1310, 0.0304},  // wsx_m32n32w8d2
+};
+
+// Shapes without a table entry, no split. Above 128 tokens a wave-quantization cost model
+// picks the tile: a launch of T workgroups on 256 CUs takes ceil(T / 256) rounds, and a
+// round of tile t costs c_t + d_t * K * TM * TN / 1e9 (kTileCost). With few tokens, rules
+// from a sweep of the weight-streaming and deep-ring tiles pick it; select_plan refines
+// them above 16 tokens.
 int fallback_tile(int64_t M, int64_t N, int64_t K) {
     const int64_t cus = 256;
     if (M > 128) {
@@ -1798,30 +1831,147 @@ const TileInfo *tile_info(int id) {
 
 int default_tile(int64_t M, int64_t N, int64_t K) { return fallback_tile(M, N, K); }
 
-int select_tile(int64_t M, int64_t N, int64_t K) {
+// The table's tile for a shape, -1 without an entry.
+static int table_tile(int64_t M, int64_t N, int64_t K) {
     for (const TableEntry &e : kTileTable) {
         if (e.n == N && e.k == K && M >= e.m_lo && M <= e.m_hi && e.tile >= 0 &&
             e.tile < kNumTiles)
             return e.tile;
     }
-    return fallback_tile(M, N, K);
+    return -1;
 }
 
-// Splits of a split tile for K: panels of BK bytes dealt out in equal runs; a short K
-// gets fewer splits (one: no split at all).
-static int split_count(const TileInfo &t, int64_t K, int *chunk) {
+int select_tile(int64_t M, int64_t N, int64_t K) {
+    const int t = table_tile(M, N, K);
+    return t >= 0 ? t : fallback_tile(M, N, K);
+}
+
+// Splits of a plan for K: panels of BK bytes dealt out in equal runs of *chunk bytes; a
+// short K gets fewer splits (one: no split at all).
+static int split_count(const TileInfo &t, int splits, int64_t K, int *chunk) {
     const int64_t panels = (K + t.bk - 1) / t.bk;
-    const int64_t per = (panels + t.ksplit - 1) / t.ksplit;
+    const int64_t per = (panels + splits - 1) / splits;
     if (chunk)
         *chunk = (int)(per * t.bk);
     return per > 0 ? (int)((panels + per - 1) / per) : 1;
 }
 
-size_t tile_workspace_bytes(int id, int64_t M, int64_t N, int64_t K) {
-    if (id < 0 || id >= kNumTiles || kTiles[id].info.ksplit <= 1)
+GemmPlan tile_plan(int id) {
+    return GemmPlan{id, id >= 0 && id < kNumTiles ? kTiles[id].info.ksplit : 1};
+}
+
+size_t plan_workspace_bytes(const GemmPlan &p, int64_t M, int64_t N, int64_t K) {
+    if (p.tile < 0 || p.tile >= kNumTiles || p.splits <= 1)
         return 0;
-    const int splits = split_count(kTiles[id].info, K, nullptr);
+    const int splits = split_count(kTiles[p.tile].info, p.splits, K, nullptr);
     return splits > 1 ? (size_t)splits * (size_t)M * (size_t)N * sizeof(int32_t) : 0;
+}
+
+// Predicted time in us of an LDS-staged tile on `tiles` output tiles, with K divided among
+// `splits` workgroups for each. (32-bit counts: this runs on every call.)
+static double plan_cost_us(int id, uint32_t tiles, uint32_t splits, double mn, uint32_t K) {
+    const TileInfo &t = kTiles[id].info;
+    uint32_t n = 1, k = K;
+    if (splits > 1) {
+        const uint32_t panels = (K + t.bk - 1) / t.bk, per = (panels + splits - 1) / splits;
+        n = (panels + per - 1) / per;
+        if (n > 1)
+            k = per * t.bk;
+    }
+    const double round = kTileCost[id].c + kTileCost[id].d * 1e-9 * (double)(t.tm * t.tn) * k;
+    double us = 1e3 * (double)((tiles * n + 255) / 256) * round;
+    if (n > 1)
+        us += kSplitFixedUs + kSplitUs * n + kSplitUsPerMB * 4e-6 * n * mn;
+    return us;
+}
+
+static double stream_cost_us(const StreamCost &c, int64_t M, int64_t N, int64_t K) {
+    const TileInfo &t = kTiles[c.tile].info;
+    const int64_t wgs = ((M + t.tm - 1) / t.tm) * ((N + t.tn - 1) / t.tn);
+    const int64_t rows = M < t.tm ? M : t.tm;
+    return c.fixed + c.k * 1e-3 * (double)K + c.round * (double)((wgs + 255) / 256) +
+           1e-6 * (double)(wgs * K) * (c.w * t.tn + c.x * (double)rows);
+}
+
+// What runs a shape by default. Up to 16 tokens, and where the operands take the any-
+// alignment kernels, the selected tile. Above, the least predicted time over the tiles,
+// each unsplit and with K split in as many ways as fit one round of workgroups; a table
+// entry stays unless the prediction beats its own clearly. On 1100 random shapes (M
+// 17..8192, N 128..20480, K 256..24576) the choice is within 1.8% of the fastest plan above
+// 128 tokens (geometric mean; 5% below 32, 3.4% up to 64, 1.5% up to 128), where the table's
+// fallback was 22% off (12, 16 and 28%): long K on few output tiles left most CUs idle
+// (512 x 4608 x 53248: 162.7 us split in two, 137.9 in three on 216 workgroups), and tiles
+// without a deep ring were taken for small outputs (640 x 1024 x 4096: 20.7 against 11.0 us).
+static GemmPlan compute_plan(int64_t M, int64_t N, int64_t K) {
+    const int table = table_tile(M, N, K);
+    GemmPlan best = tile_plan(table >= 0 ? table : fallback_tile(M, N, K));
+    if (M <= 16 || K < 16 || K % 16 != 0 || M > (1 << 20) || N > (1 << 20))
+        return best;
+    const uint32_t m = (uint32_t)M, n = (uint32_t)N, k = (uint32_t)K;
+    const double mn = (double)M * (double)N;
+    const auto tiles_of = [&](const TileInfo &t) {
+        return ((m + t.tm - 1) / (uint32_t)t.tm) * ((n + t.tn - 1) / (uint32_t)t.tn);
+    };
+    double limit = -1.0;               // none yet
+    if (table >= 0) {
+        const TileInfo &bt = kTiles[table].info;
+        const int base = bt.base >= 0 ? bt.base : table;
+        if (!(kTileCost[base].d > 0.0))
+            return best;
+        limit = kOverTable * plan_cost_us(base, tiles_of(bt), best.splits, mn, k);
+    }
+    const auto consider = [&](int id, uint32_t splits, double us) {
+        if (limit < 0.0 || us < limit) {
+            limit = us;
+            best = GemmPlan{id, (int)splits};
+        }
+    };
+    if (M <= 128)
+        for (const StreamCost &c : kStreamCost)
+            consider(c.tile, 1, stream_cost_us(c, M, N, K));
+    const uint32_t by_space = (uint32_t)(kSplitWorkspace / 4 / (mn > 1.0 ? mn : 1.0));
+    for (int id = 0; id < kNumTiles; ++id) {
+        const TileInfo &t = kTiles[id].info;
+        if (t.base >= 0 || !(kTileCost[id].d > 0.0))
+            continue;
+        const uint32_t tiles = tiles_of(t);
+        consider(id, 1, plan_cost_us(id, tiles, 1, mn, k));
+    }
+    const double unsplit = table >= 0 ? limit / kOverTable : limit;
+    for (int id = 0; id < kNumTiles && unsplit > kSplitWorthUs; ++id) {
+        const TileInfo &t = kTiles[id].info;
+        if (t.base >= 0 || !t.splittable || !(kTileCost[id].d > 0.0))
+            continue;
+        const uint32_t tiles = tiles_of(t);
+        if (tiles > 128)
+            continue;
+        // One round of workgroups, at least four panels each.
+        const uint32_t panels = k / (uint32_t)t.bk;
+        uint32_t most = 256 / tiles;
+        most = std::min({most, kMaxSplits, by_space, panels / 4});
+        for (uint32_t splits = 2; splits < most; splits += 1 + splits / 4)
+            consider(id, splits, plan_cost_us(id, tiles, splits, mn, k));
+        if (most >= 2)
+            consider(id, most, plan_cost_us(id, tiles, most, mn, k));
+    }
+    return best;
+}
+
+// The choice is a pure function of the sizes, and the calls of a program repeat few of
+// them: each thread keeps the last ones it computed (computing takes 1-2 us of host time,
+// which every call of a host-bound program would pay twice).
+GemmPlan select_plan(int64_t M, int64_t N, int64_t K) {
+    struct Entry {
+        int64_t m = -1, n = -1, k = -1;
+        GemmPlan plan = {};
+    };
+    static thread_local Entry kept[64];
+    const uint64_t h = ((uint64_t)M * 0x9E3779B97F4A7C15u) ^ ((uint64_t)N * 0xC2B2AE3D27D4EB4Fu) ^
+                       ((uint64_t)K * 0x165667B19E3779F9u);
+    Entry &e = kept[h >> 58];
+    if (e.m != M || e.n != N || e.k != K)
+        e = Entry{M, N, K, compute_plan(M, N, K)};
+    return e.plan;
 }
 
 // LDS of one workgroup on gfx950.
@@ -1900,9 +2050,9 @@ hipError_t launch_linear_small(const uint16_t *x, const int8_t *wq, const float 
     return t.launch(EPI_BF16, kp, stream);
 }
 
-hipError_t launch_gemm(int id, Epilogue epi, bool vec, const GemmArgs &a, void *ws,
+hipError_t launch_gemm(const GemmPlan &plan, Epilogue epi, bool vec, const GemmArgs &a, void *ws,
                        size_t ws_bytes, hipStream_t stream) {
-    const TileEntry &t = kTiles[id];
+    const TileEntry &t = kTiles[plan.tile];
     const int tm = t.info.tm, tn = t.info.tn;
     KParams kp;
     kp.a = a;
@@ -1925,11 +2075,11 @@ hipError_t launch_gemm(int id, Epilogue epi, bool vec, const GemmArgs &a, void *
     kp.x = nullptr;
     if (!vec)
         return launch_any(epi, kp, stream);
-    if (t.info.ksplit > 1) {
+    if (plan.splits > 1) {
         int chunk = 0;
-        const int splits = split_count(t.info, a.K, &chunk);
+        const int splits = split_count(t.info, plan.splits, a.K, &chunk);
         if (splits > 1) {
-            if (ws == nullptr || ws_bytes < tile_workspace_bytes(id, a.M, a.N, a.K))
+            if (ws == nullptr || ws_bytes < plan_workspace_bytes(plan, a.M, a.N, a.K))
                 return hipErrorInvalidValue;
             kp.k_split = splits;
             kp.k_chunk = chunk;

@@ -54,17 +54,19 @@ w8a8_status check_gemm(const int8_t *xq, const int8_t *wq, const void *out, int6
     return W8A8_OK;
 }
 
-w8a8_status run_gemm(const int8_t *xq, const float *sx, const int8_t *wq, const float *sw,
+// The plan that a workspace of ws_bytes allows: the default one, or the selected tile as it
+// is where the default's partials do not fit. False if neither fits.
+bool plan_within(GemmPlan &plan, int64_t M, int64_t N, int64_t K, size_t ws_bytes) {
+    if (plan_workspace_bytes(plan, M, N, K) <= ws_bytes)
+        return true;
+    plan = tile_plan(select_tile(M, N, K));
+    return plan_workspace_bytes(plan, M, N, K) <= ws_bytes;
+}
+
+w8a8_status run_plan(const int8_t *xq, const float *sx, const int8_t *wq, const float *sw,
                      const uint16_t *bias, void *out, Epilogue epi, int64_t M, int64_t N,
-                     int64_t K, void *ws, size_t ws_bytes, int tile_id, hipStream_t s) {
-    if (tile_id < -1 || tile_id >= tile_count())
-        return W8A8_ERR_ARG;
-    if (M == 0 || N == 0)
-        return W8A8_OK;
-    const int id = tile_id >= 0 ? tile_id : select_tile(M, N, K);
-    const size_t need = tile_workspace_bytes(id, M, N, K);
-    if (need > 0 && (ws == nullptr || ws_bytes < need))
-        return W8A8_ERR_WORKSPACE;
+                     int64_t K, void *ws, size_t ws_bytes, const GemmPlan &plan,
+                     hipStream_t s) {
     GemmArgs a;
     a.xq = xq;
     a.wq = wq;
@@ -76,7 +78,22 @@ w8a8_status run_gemm(const int8_t *xq, const float *sx, const int8_t *wq, const 
     a.N = N;
     a.K = K;
     const bool vec = (K % 16 == 0) && aligned16(xq) && aligned16(wq);
-    return from_hip(launch_gemm(id, epi, vec, a, ws, ws_bytes, s));
+    return from_hip(launch_gemm(plan, epi, vec, a, ws, ws_bytes, s));
+}
+
+w8a8_status run_gemm(const int8_t *xq, const float *sx, const int8_t *wq, const float *sw,
+                     const uint16_t *bias, void *out, Epilogue epi, int64_t M, int64_t N,
+                     int64_t K, void *ws, size_t ws_bytes, int tile_id, hipStream_t s) {
+    if (tile_id < -1 || tile_id >= tile_count())
+        return W8A8_ERR_ARG;
+    if (M == 0 || N == 0)
+        return W8A8_OK;
+    const size_t have = ws ? ws_bytes : 0;
+    GemmPlan plan = tile_id >= 0 ? tile_plan(tile_id) : select_plan(M, N, K);
+    if (tile_id >= 0 ? plan_workspace_bytes(plan, M, N, K) > have
+                     : !plan_within(plan, M, N, K, have))
+        return W8A8_ERR_WORKSPACE;
+    return run_plan(xq, sx, wq, sw, bias, out, epi, M, N, K, ws, ws_bytes, plan, s);
 }
 
 // Scratch of w8a8_linear_noalloc: Xq, sx and the GEMM's split-K partials, laid out as
@@ -177,7 +194,7 @@ size_t w8a8_gemm_workspace_bytes_ex(int64_t M, int64_t N, int64_t K, int tile_id
     if (M <= 0 || N <= 0 || K < 0 || K > W8A8_MAX_K || tile_id < -1 ||
         tile_id >= tile_count() || !product_ok(M, N))
         return 0;
-    return tile_workspace_bytes(tile_id >= 0 ? tile_id : select_tile(M, N, K), M, N, K);
+    return plan_workspace_bytes(tile_id >= 0 ? tile_plan(tile_id) : select_plan(M, N, K), M, N, K);
 }
 
 size_t w8a8_gemm_workspace_bytes(int64_t M, int64_t N, int64_t K) {
@@ -212,6 +229,23 @@ size_t w8a8_linear_workspace_bytes(int64_t M, int64_t N, int64_t K) {
            w8a8_gemm_workspace_bytes(M, N, K);
 }
 
+size_t w8a8_gemm_workspace_least_bytes(int64_t M, int64_t N, int64_t K) {
+    if (M <= 0 || N <= 0 || K < 0 || K > W8A8_MAX_K || !product_ok(M, N))
+        return 0;
+    const size_t a = plan_workspace_bytes(select_plan(M, N, K), M, N, K);
+    if (a == 0)
+        return 0;
+    const size_t b = plan_workspace_bytes(tile_plan(select_tile(M, N, K)), M, N, K);
+    return a < b ? a : b;
+}
+
+size_t w8a8_linear_workspace_least_bytes(int64_t M, int64_t N, int64_t K) {
+    if (M <= 0 || N < 0 || K < 0 || !product_ok(M, K))
+        return 0;
+    return align_up((size_t)(M * K)) + align_up((size_t)M * sizeof(float)) +
+           w8a8_gemm_workspace_least_bytes(M, N, K);
+}
+
 w8a8_status w8a8_linear_ex(const uint16_t *x, int act, const float *col_mul,
                            const int8_t *wq, const float *w_scale, const uint16_t *bias,
                            uint16_t *y, int64_t M, int64_t N, int64_t K, void *workspace,
@@ -227,8 +261,15 @@ w8a8_status w8a8_linear_ex(const uint16_t *x, int act, const float *col_mul,
         return W8A8_OK;
     if (!y || !w_scale || (K > 0 && (!x || !wq)))
         return W8A8_ERR_NULL;
-    const size_t need = w8a8_linear_workspace_bytes(M, N, K);
-    if (!workspace || workspace_bytes < need)
+    const size_t head = align_up((size_t)(M * K)) + align_up((size_t)M * sizeof(float));
+    if (!workspace || workspace_bytes < head)
+        return W8A8_ERR_WORKSPACE;
+    // Few tokens, plain rule: quantizer and GEMM in one launch (the workspace is unused).
+    const bool one_launch =
+        act == W8A8_ACT_NONE && !col_mul && linear_small_applies(M, N, K, x, wq);
+    GemmPlan plan = one_launch ? tile_plan(select_tile(M, N, K)) : select_plan(M, N, K);
+    const size_t gws_bytes = workspace_bytes - head;
+    if (!plan_within(plan, M, N, K, gws_bytes))
         return W8A8_ERR_WORKSPACE;
     if (reinterpret_cast<uintptr_t>(workspace) % kAlign != 0)
         return W8A8_ERR_WORKSPACE;
@@ -237,14 +278,12 @@ w8a8_status w8a8_linear_ex(const uint16_t *x, int act, const float *col_mul,
                                           align_up((size_t)(M * K)));
     char *gws = reinterpret_cast<char *>(sx) + align_up((size_t)M * sizeof(float));
     hipStream_t s = as_stream(stream);
-    // Few tokens, plain rule: quantizer and GEMM in one launch (the workspace is unused).
-    if (act == W8A8_ACT_NONE && !col_mul && linear_small_applies(M, N, K, x, wq))
+    if (one_launch)
         return from_hip(launch_linear_small(x, wq, w_scale, bias, y, M, N, K, s));
     hipError_t e = launch_quant_rows(x, M, K, act, col_mul, xq, sx, s);
     if (e != hipSuccess)
         return W8A8_ERR_HIP;
-    return run_gemm(xq, sx, wq, w_scale, bias, y, EPI_BF16, M, N, K, gws,
-                    workspace_bytes - (size_t)(gws - static_cast<char *>(workspace)), -1, s);
+    return run_plan(xq, sx, wq, w_scale, bias, y, EPI_BF16, M, N, K, gws, gws_bytes, plan, s);
 }
 
 w8a8_status w8a8_linear(const uint16_t *x, const int8_t *wq, const float *w_scale,
@@ -271,7 +310,7 @@ w8a8_status w8a8_linear_noalloc(const uint16_t *x, int act, const float *col_mul
         return W8A8_OK;
     if (!y || !w_scale || (K > 0 && (!x || !wq)))
         return W8A8_ERR_NULL;
-    const size_t need = w8a8_linear_workspace_bytes(M, N, K);
+    const size_t need = w8a8_linear_workspace_least_bytes(M, N, K);
     if (need > W8A8_NOALLOC_SCRATCH_BYTES)
         return W8A8_ERR_SCRATCH;
     void *ptr = nullptr;
@@ -295,7 +334,7 @@ w8a8_status w8a8_gemm_acc_i32_ex(const int8_t *xq, const int8_t *wq, int32_t *ac
     // The debug accumulator has no workspace: a split tile runs unsplit.
     if (tile_info(id)->base >= 0)
         id = tile_info(id)->base;
-    if (tile_workspace_bytes(id, M, N, K) > 0)
+    if (plan_workspace_bytes(tile_plan(id), M, N, K) > 0)
         return W8A8_ERR_ARG;
     return run_gemm(xq, nullptr, wq, nullptr, nullptr, acc, EPI_I32, M, N, K, nullptr, 0,
                     id, as_stream(stream));

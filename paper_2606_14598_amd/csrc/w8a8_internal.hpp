@@ -44,7 +44,13 @@ struct TileInfo {
     int lds_bytes;       // static LDS per workgroup
     int ksplit;          // K divided among this many workgroups per tile (1: no split)
     int base;            // for a split tile, the id of the same tile unsplit (else -1)
-    int streaming;       // 1: the weight-streaming kernel for few tokens
+    int streaming;       // 1, 2: a weight-streaming kernel for few tokens
+    bool splittable;     // its kernel can divide K among workgroups
+};
+
+// A tile with K divided among `splits` workgroups per output tile.
+struct GemmPlan {
+    int tile, splits;
 };
 
 int tile_count();
@@ -53,12 +59,16 @@ const TileInfo *tile_info(int id);
 int select_tile(int64_t M, int64_t N, int64_t K);
 // The fallback rule alone (what a shape gets without a table entry).
 int default_tile(int64_t M, int64_t N, int64_t K);
-// Extra device scratch a tile needs for a shape: the int32 partial products of a split
-// tile (splits x M x N x 4 bytes), 0 for the others.
-size_t tile_workspace_bytes(int id, int64_t M, int64_t N, int64_t K);
-// Launch tile `id` with epilogue `epi`; `vec` selects the 16-byte-aligned load path.
-hipError_t launch_gemm(int id, Epilogue epi, bool vec, const GemmArgs &a, void *ws,
-                       size_t ws_bytes, hipStream_t stream);
+// The plan of tile `id` as registered, and the one that runs a shape by default: the
+// selected tile, or a tile with K split where that leaves fewer CUs idle.
+GemmPlan tile_plan(int id);
+GemmPlan select_plan(int64_t M, int64_t N, int64_t K);
+// Extra device scratch a plan needs for a shape: the int32 partial products of a split
+// one (splits x M x N x 4 bytes), 0 for the others.
+size_t plan_workspace_bytes(const GemmPlan &p, int64_t M, int64_t N, int64_t K);
+// Launch a plan with epilogue `epi`; `vec` selects the 16-byte-aligned load path.
+hipError_t launch_gemm(const GemmPlan &plan, Epilogue epi, bool vec, const GemmArgs &a,
+                       void *ws, size_t ws_bytes, hipStream_t stream);
 
 // The small fused linear: quantizer and GEMM in one launch, for shapes whose chosen tile
 // is a weight-streaming one and whose token blocks are small enough to be quantized by

@@ -154,48 +154,13 @@ def _tile_dims(name):
     return tuple(int(g) for g in m.groups()) if m else None
 
 
-def tile_costs(results, names):
-    """Per-round cost model of each LDS-staged tile, fitted to the sweep: a launch of T
-    workgroups takes ceil(T / CUS) rounds, each costing c + d * (K * TM * TN / 1e9) ms
-    (c: the fixed part of a round -- launch share, prologue, epilogue; d: the
-    per-multiply-accumulate part). Least squares on relative error over the swept shapes
-    with more than 128 tokens; c is held at 0 if it fits negative. (0, 0) for the
-    weight-streaming and split-K tiles (not modeled)."""
-    out = []
-    for n in names:
-        d = _tile_dims(n)
-        rows, ys = [], []
-        if d is not None and "_k" not in n:
-            for r in results:
-                if r["M"] <= 128 or n not in r["ms"]:
-                    continue
-                tiles = -(-r["M"] // d[0]) * -(-r["N"] // d[1])
-                rounds = -(-tiles // CUS)
-                rows.append([rounds, rounds * r["K"] * d[0] * d[1] / 1e9])
-                ys.append(r["ms"][n])
-        if len(rows) < 2:
-            out.append((0.0, 0.0))
-            continue
-        A = np.array(rows)
-        y = np.array(ys)
-        w = 1.0 / y
-        c, dd = np.linalg.lstsq(A * w[:, None], y * w, rcond=None)[0]
-        if c < 0:
-            c = 0.0
-            dd = float(np.sum(A[:, 1] * w * w * y) / np.sum((A[:, 1] * w) ** 2))
-        out.append((float(c), float(dd)) if dd > 0 else (0.0, 0.0))
-    return out
-
-
 def write_table(results, path):
     names = [w8a8.tile_name(t) for t in range(w8a8.tile_count())]
-    costs = tile_costs(results, names)
-    lines = [HEADER, "// Fallback cost model per tile: {c, d}, one round = c + d * K * TM * TN / 1e9 ms.",
-             "static const TileCost kTileCost[] = {"]
-    for n, (c, dd) in zip(names, costs):
-        lines.append(f"    {{{c:.6e}, {dd:.6e}}},  // {n}")
-    lines.append("};")
-    lines.append("")
+    # the cost model is fitted to random shapes, not to these: it stays as it is
+    old = open(os.path.join(os.path.dirname(os.path.abspath(__file__)), "csrc",
+                            "tile_table.inc")).read()
+    costs = old[old.index("// Cost model per tile"):old.index("static const TableEntry")]
+    lines = [HEADER, costs.rstrip(), ""]
     lines.append("static const TableEntry kTileTable[] = {")
     for r in results:
         lines.append(f"    {{{r['m_lo']}, {r['m_hi']}, {r['N']}, {r['K']}, "
