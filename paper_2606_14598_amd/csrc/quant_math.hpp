@@ -7,6 +7,7 @@
 
 #include <hip/hip_runtime.h>
 #include <stdint.h>
+#include <type_traits>
 
 namespace w8a8 {
 
@@ -37,11 +38,21 @@ __device__ __forceinline__ uint32_t absmax8(uint4 d) {
     return m;
 }
 
+// Maximum over the wavefront, the same in every lane: four steps inside the rows of 16
+// lanes, two across them (lane 63 then holds the maximum), all in DPP operands; a shuffle
+// tree goes through LDS six times.
 __device__ __forceinline__ uint32_t wave_max(uint32_t v) {
-#pragma unroll
-    for (int off = 32; off >= 1; off >>= 1)
-        v = max(v, (uint32_t)__shfl_xor((int)v, off, 64));
-    return v;
+    const auto step = [&](auto ctrl) {
+        v = max(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, decltype(ctrl)::value, 0xF,
+                                                         0xF, true));
+    };
+    step(std::integral_constant<int, 0x111>{});   // row_shr:1
+    step(std::integral_constant<int, 0x112>{});   // row_shr:2
+    step(std::integral_constant<int, 0x114>{});   // row_shr:4
+    step(std::integral_constant<int, 0x118>{});   // row_shr:8
+    step(std::integral_constant<int, 0x142>{});   // row_bcast:15
+    step(std::integral_constant<int, 0x143>{});   // row_bcast:31
+    return (uint32_t)__builtin_amdgcn_readlane((int)v, 63);
 }
 
 // Codes of four values: clamp(rne(v * inv), -127, 127) as bytes, the first lowest. The

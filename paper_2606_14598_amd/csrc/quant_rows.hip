@@ -13,13 +13,12 @@
 // of Section 3 smooths the activations by 1/s[k] and folds s[k] into the weights).
 // Both are evaluated in float32; the row maximum is then taken on float32 values.
 //
-// The kernel is HBM-bound (3 bytes moved per element: 2 read, 1 written), or ALU-bound
-// with GELU. Rows whose K fits the register file (K <= 65536 for the plain rule) are read
-// once with 16-byte loads, kept in VGPRs for the second (quantizing) pass and written
-// with 16-byte streaming stores where alignment allows (8-byte stores otherwise), by a
-// persistent grid that prefetches the next rows while it finishes the current ones; the
-// row maximum is taken on the bf16 bit patterns (|v| ordered as an unsigned integer,
-// exact for finite values) with a wavefront butterfly and, for rows of several
+// The kernel is HBM-bound (3 bytes moved per element: 2 read, 1 written). Rows whose K fits
+// the register file (K <= 65536 for the plain rule) are read once with 16-byte loads, kept in
+// VGPRs for the second (quantizing) pass and written with 16-byte stores, streaming where
+// alignment allows, by a persistent grid that prefetches the next rows while it finishes the
+// current ones; the row maximum is taken on the bf16 bit patterns (|v| ordered as an unsigned
+// integer, exact for finite values) with a wavefront reduction and, for rows of several
 // wavefronts, one LDS exchange. Longer rows are read twice by a looped kernel.
 #include "w8a8_internal.hpp"
 #include "quant_math.hpp"
@@ -30,6 +29,13 @@ namespace {
 using namespace qmath;
 
 typedef uint32_t u32x4v __attribute__((ext_vector_type(4)));
+typedef uint32_t u32x2v __attribute__((ext_vector_type(2)));
+
+// Buffer-resource word 3 for gfx9 (raw 32-bit data format, no swizzle), an offset beyond any
+// row (loads give zero, stores are dropped), and the streaming cache policy of a store.
+constexpr int kRsrcWord3 = 0x00020000;
+constexpr int kOutside = 0x7FFFFF00;
+constexpr int kStreaming = 2;
 
 // Swap with the neighbouring lane (lane l <-> l ^ 1) by a DPP quad permutation [1,0,3,2].
 __device__ __forceinline__ uint32_t swap_lane_pair(uint32_t v) {
@@ -63,12 +69,13 @@ __device__ __forceinline__ float gelu_f32(float x) {
     return 0.5f * x * (x < 0.0f ? e : 2.0f - e);
 }
 
-// The same factor from a table: the inputs are bf16, so erfc(|x| / sqrt(2)) / 2 takes one
-// value per magnitude. Below 2^-24 it is 1/2 to float32 precision and from 16 up it is 0,
-// so the 28 binades between (128 magnitudes each) and the end cover every input. The
-// entries are computed here at compile time in double: a series up to z = 1.5, the
-// continued fraction of erfc above.
-constexpr int kGeluLo = (127 - 24) << 7, kGeluHi = (127 + 4) << 7;   // bf16 magnitude bits
+// The same factor from a table: the inputs are bf16, so h = erfc(|x| / sqrt(2)) / 2 takes one
+// value per magnitude. From 16 up it is 0; below 2^-8 it is 1/2 - |x| / sqrt(2 pi) to within
+// |x|^3 / 15 (4e-9). The 12 binades between (128 magnitudes each) and the end make 6 KB, which
+// every block copies to LDS: with 28 binades (down to 2^-24, where h is 1/2) the copy cost
+// short calls 0.3 us more. The entries are computed here at compile time in double: a series
+// up to z = 1.5, the continued fraction of erfc above.
+constexpr int kGeluLo = (127 - 8) << 7, kGeluHi = (127 + 4) << 7;   // bf16 magnitude bits
 constexpr int kGeluN = kGeluHi - kGeluLo + 1;
 
 constexpr double exp_nonpos(double x) {
@@ -111,9 +118,9 @@ constexpr GeluTable make_gelu_table() {
     GeluTable t{};
     for (int i = 0; i + 1 < kGeluN; ++i) {
         double x = 1.0 + (i & 127) / 128.0;
-        for (int e = i >> 7; e < 24; ++e)
+        for (int e = i >> 7; e < 8; ++e)
             x *= 0.5;
-        for (int e = 24; e < (i >> 7); ++e)
+        for (int e = 8; e < (i >> 7); ++e)
             x *= 2.0;
         const double h = 0.5 * erfc_const(x * 0.70710678118654752440);
         t.h[i] = h < 1e-45 ? 0.0f : (float)h;
@@ -126,8 +133,11 @@ __device__ const GeluTable kGeluTable = make_gelu_table();
 // for x < 0 and 1 - h(|x|) otherwise, the table in LDS.
 __device__ __forceinline__ float gelu_lookup(uint32_t h, const float *table) {
     const float x = bf16_to_f32(h);
-    const int i = min(max((int)(h & 0x7FFFu), kGeluLo), kGeluHi) - kGeluLo;
-    const float e = table[i];
+    const int mag = (int)(h & 0x7FFFu);
+    const float tail = table[min(max(mag, kGeluLo), kGeluHi) - kGeluLo];
+    const float e = mag < kGeluLo
+                        ? __builtin_fmaf(__builtin_fabsf(x), -0.39894228040143267794f, 0.5f)
+                        : tail;
     return x * (x < 0.0f ? e : 1.0f - e);
 }
 
@@ -184,6 +194,14 @@ __device__ __forceinline__ uint4 load8_any(const uint16_t *row, int64_t vi, int6
 // same for every row, so its multipliers are loaded once into registers; the
 // transformed row is held as float32 between the maximum and the coding pass.
 //
+// Loads and stores go through a buffer descriptor of the row (lanes past its end, and rows
+// past the last, read zeros and store nothing) and so need no branches: with a branch around
+// a load the compiler cannot count the loads in flight and waits for all of them, the next
+// row's included. With that, the wavefront maximum in DPP operands and one barrier per row
+// instead of two, us for branches and shuffles -> now: 4096 x 2048 6.7 -> 5.6, 2048 x 4096
+// 7.0 -> 5.9, 77 x 4096 3.1 -> 2.7, 4096 x 7696 22.1 -> 19.6 (4.8 TB/s); with GELU and the
+// multiplier 4096 x 16384 47 -> 42.
+//
 // ANY: rows at any alignment and any K >= 8, by the same 16-byte loads and 8-byte stores
 // at the rows' own alignment. The vector that crosses the row's end is read as the row's
 // last 8 elements shifted down, zeros behind, and its codes are stored one by one.
@@ -196,14 +214,17 @@ quant_rows_reg(const uint16_t *__restrict__ v, int64_t rows, int64_t K,
                const float *__restrict__ colmul, int8_t *__restrict__ q,
                float *__restrict__ scale) {
     constexpr bool PLAIN = ACT == ACT_NONE && !CM;
-    constexpr int RPB = reg_block_threads<TPR>() / TPR;
+    constexpr int BS = reg_block_threads<TPR>();
+    constexpr int RPB = BS / TPR;
+    constexpr int WPR = TPR / 64;              // wavefronts per row
     const int t = threadIdx.x % TPR;
-    const int sub = threadIdx.x / TPR;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int sub = wave / WPR;
     const int64_t nvec = (K + 7) >> 3;
     const int64_t nwhole = K >> 3;             // vectors that lie wholly in the row
     const int64_t groups = (rows + RPB - 1) / RPB;
-    const bool wide = !ANY && (K % 16 == 0) && (reinterpret_cast<uintptr_t>(q) % 16 == 0);
-    __shared__ uint32_t part[RPB][TPR / 64];
+    const bool wide = (K % 16 == 0) && (reinterpret_cast<uintptr_t>(q) % 16 == 0);
+    __shared__ uint32_t part[2][RPB][WPR];     // in turn, so one barrier per row will do
     constexpr bool GELU = ACT == ACT_GELU;
     __shared__ __attribute__((aligned(16))) float gelu[GELU ? sizeof(GeluTable) / 4 : 1];
 
@@ -234,25 +255,27 @@ quant_rows_reg(const uint16_t *__restrict__ v, int64_t rows, int64_t K,
         }
     }
 
-    auto load = [&](uint4 (&d)[NV], int64_t grp) {
+    auto load = [&](uint4 (&d)[NV], int64_t grp) __attribute__((always_inline)) {
         const int64_t row = grp * RPB + sub;
-        const bool live = grp < groups && row < rows;
+        const bool live = row < rows;
         const uint16_t *base = v + (live ? row : 0) * K;
-        const uint4 *src = reinterpret_cast<const uint4 *>(base);
+        const __amdgpu_buffer_rsrc_t src = __builtin_amdgcn_make_buffer_rsrc(
+            (void *)base, (short)0, live ? (int)(2 * K) : 0, kRsrcWord3);
 #pragma unroll
         for (int j = 0; j < NV; ++j) {
-            const int64_t vi = (int64_t)j * TPR + t;
-            d[j] = make_uint4(0, 0, 0, 0);
             if constexpr (ANY) {
+                const int64_t vi = (int64_t)j * TPR + t;
+                d[j] = make_uint4(0, 0, 0, 0);
                 if (live && vi < nvec)
                     d[j] = load8_any(base, vi, nwhole, K);
             } else {
-                if (live && vi < nvec)
-                    d[j] = src[vi];
+                const u32x4v w = __builtin_amdgcn_raw_buffer_load_b128(src, (j * TPR + t) * 16, 0, 0);
+                d[j] = make_uint4(w.x, w.y, w.z, w.w);
             }
         }
     };
-    auto process = [&](const uint4 (&d)[NV], int64_t grp) {
+    int turn = 0;
+    auto process = [&](const uint4 (&d)[NV], int64_t grp) __attribute__((always_inline)) {
         const int64_t row = grp * RPB + sub;
         uint32_t m = 0;
         float f[PLAIN ? 1 : NV][8];
@@ -277,22 +300,16 @@ quant_rows_reg(const uint16_t *__restrict__ v, int64_t rows, int64_t K,
             m = __float_as_uint(fm);   // |v| >= 0: its bit pattern orders like the value
         }
         m = wave_max(m);
-        if constexpr (TPR > 64) {
-            constexpr int WPR = TPR / 64;   // wavefronts per row
+        if constexpr (WPR > 1) {
             if ((threadIdx.x & 63) == 0)
-                part[sub][(threadIdx.x >> 6) % WPR] = m;
+                part[turn][sub][wave % WPR] = m;
             __syncthreads();
 #pragma unroll
             for (int w = 0; w < WPR; ++w)
-                m = max(m, part[sub][w]);
-            __syncthreads();   // part is rewritten by the next row group
+                m = max(m, part[turn][sub][w]);
+            turn ^= 1;
         }
         const RowScale rs = PLAIN ? row_scale(m) : row_scale_f(__uint_as_float(m));
-        if (row >= rows)
-            return;
-        if (t == 0)
-            scale[row] = rs.scale;
-        uint2 *dst = reinterpret_cast<uint2 *>(q + row * K);
         // Codes of vector j of this lane (8 bytes).
         auto codes = [&](int j) __attribute__((always_inline)) {
             uint2 o;
@@ -304,50 +321,12 @@ quant_rows_reg(const uint16_t *__restrict__ v, int64_t rows, int64_t K,
             }
             return o;
         };
-        // Transformed rows with the multiplier and an even count of four or more vectors
-        // keep 8-byte stores: the swaps push their registers past what hides the loads
-        // (4608 x 16384 with GELU on 512 x 4: 66.5 us paired, 52.2 not; elsewhere pairs
-        // are up to 15% faster, 4110 x 4608 on 256 x 3: 12.5 against 14.7 us).
-        constexpr bool PAIRS = PLAIN || !CM || NV <= 3 || NV % 2 == 1;
-        if (PAIRS && wide) {
-            // 16-byte streaming stores (K % 16 == 0, q 16-byte aligned), one pair of
-            // vectors at a time. Vectors j and j+1 of lane t are j*TPR + t and
-            // (j+1)*TPR + t; neighbouring lanes swap one code word pair so that the even
-            // lane holds vectors j*TPR + t, +1 and the odd lane (j+1)*TPR + t - 1, +1.
-            // Streaming 16-byte stores leave no dirty lines in this XCD's L2 for the
-            // kernel's end to write back before the consumer starts (plain stores, and
-            // 8-byte streaming ones, delayed the next kernel by 1.5-2.5 us).
-            const bool odd = t & 1;
-#pragma unroll
-            for (int j = 0; j + 1 < NV; j += 2) {
-                // Selects on scalars (a select between array elements would put the
-                // array in memory).
-                const uint2 ca = codes(j), cb = codes(j + 1);
-                const uint32_t a0 = ca.x, a1 = ca.y, b0 = cb.x, b1 = cb.y;
-                const uint32_t r0 = swap_lane_pair(odd ? a0 : b0);
-                const uint32_t r1 = swap_lane_pair(odd ? a1 : b1);
-                const int64_t v0 = (int64_t)(odd ? j + 1 : j) * TPR + t - (odd ? 1 : 0);
-                const u32x4v o = odd ? u32x4v{r0, r1, b0, b1} : u32x4v{a0, a1, r0, r1};
-                if (v0 + 1 < nvec)
-                    __builtin_nontemporal_store(o, reinterpret_cast<u32x4v *>(dst + v0));
-                else if (v0 < nvec)
-                    dst[v0] = make_uint2(o.x, o.y);
-            }
-            if constexpr (NV % 2 == 1) {
-                // The last vector of an odd count: the even lane of each pair takes its
-                // neighbour's codes (vector j*TPR + t + 1) and stores both.
-                const uint2 c = codes(NV - 1);
-                const uint32_t n0 = swap_lane_pair(c.x), n1 = swap_lane_pair(c.y);
-                const int64_t vi = (int64_t)(NV - 1) * TPR + t;
-                if (!odd) {
-                    if (vi + 1 < nvec)
-                        __builtin_nontemporal_store(u32x4v{c.x, c.y, n0, n1},
-                                                    reinterpret_cast<u32x4v *>(dst + vi));
-                    else if (vi < nvec)
-                        dst[vi] = c;
-                }
-            }
-        } else if constexpr (ANY) {
+        const bool live = row < rows;
+        if constexpr (ANY) {
+            if (!live)
+                return;
+            if (t == 0)
+                scale[row] = rs.scale;
 #pragma unroll
             for (int j = 0; j < NV; ++j) {
                 const int64_t vi = (int64_t)j * TPR + t;
@@ -365,11 +344,57 @@ quant_rows_reg(const uint16_t *__restrict__ v, int64_t rows, int64_t K,
                 }
             }
         } else {
+            // Only lane 0 of the row lies inside the 4 bytes of its scale.
+            const __amdgpu_buffer_rsrc_t sdst = __builtin_amdgcn_make_buffer_rsrc(
+                (void *)(scale + (live ? row : 0)), (short)0, live ? 4 : 0, kRsrcWord3);
+            __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(rs.scale), sdst, t * 4, 0, 0);
+            const __amdgpu_buffer_rsrc_t dst = __builtin_amdgcn_make_buffer_rsrc(
+                (void *)(q + (live ? row : 0) * K), (short)0, live ? (int)K : 0, kRsrcWord3);
+            // 16-byte stores, one pair of vectors at a time. Vectors j and j+1 of lane t are
+            // j*TPR + t and (j+1)*TPR + t; neighbouring lanes swap one code word pair so that
+            // the even lane holds vectors j*TPR + t, +1 and the odd lane (j+1)*TPR + t - 1,
+            // +1. Streaming stores where rows are 16-byte aligned: they leave no dirty lines
+            // in this XCD's L2 for the kernel's end to write back before the consumer starts
+            // (plain stores, and 8-byte streaming ones, delayed the next kernel by 1.5-2.5
+            // us). A row's last vector without a partner (K % 16 == 8) goes out alone.
+            constexpr int NP = (NV + 1) / 2;
+            u32x4v o[NP];
+            int v0[NP];
+            const bool odd = t & 1;
 #pragma unroll
-            for (int j = 0; j < NV; ++j) {
-                const int64_t vi = (int64_t)j * TPR + t;
-                if (vi < nvec)
-                    dst[vi] = codes(j);
+            for (int j = 0; j + 1 < NV; j += 2) {
+                // Selects on scalars (a select between array elements would put the
+                // array in memory).
+                const uint2 ca = codes(j), cb = codes(j + 1);
+                const uint32_t a0 = ca.x, a1 = ca.y, b0 = cb.x, b1 = cb.y;
+                const uint32_t r0 = swap_lane_pair(odd ? a0 : b0);
+                const uint32_t r1 = swap_lane_pair(odd ? a1 : b1);
+                o[j / 2] = odd ? u32x4v{r0, r1, b0, b1} : u32x4v{a0, a1, r0, r1};
+                v0[j / 2] = odd ? (j + 1) * TPR + t - 1 : j * TPR + t;
+            }
+            if constexpr (NV % 2 == 1) {
+                // The last vector of an odd count: the even lane of each pair takes its
+                // neighbour's codes (vector j*TPR + t + 1) and stores both.
+                const uint2 c = codes(NV - 1);
+                o[NP - 1] = u32x4v{c.x, c.y, swap_lane_pair(c.x), swap_lane_pair(c.y)};
+                v0[NP - 1] = odd ? kOutside / 8 : (NV - 1) * TPR + t;
+            }
+            if (wide) {
+#pragma unroll
+                for (int p = 0; p < NP; ++p)
+                    __builtin_amdgcn_raw_buffer_store_b128(o[p], dst, v0[p] * 8, 0, kStreaming);
+            } else {
+#pragma unroll
+                for (int p = 0; p < NP; ++p)
+                    __builtin_amdgcn_raw_buffer_store_b128(
+                        o[p], dst, v0[p] + 1 < (int)nvec ? v0[p] * 8 : kOutside, 0, 0);
+                if (nvec & 1) {
+#pragma unroll
+                    for (int p = 0; p < NP; ++p)
+                        __builtin_amdgcn_raw_buffer_store_b64(
+                            u32x2v{o[p].x, o[p].y}, dst,
+                            v0[p] + 1 == (int)nvec ? v0[p] * 8 : kOutside, 0, 0);
+                }
             }
         }
     };
@@ -378,18 +403,39 @@ quant_rows_reg(const uint16_t *__restrict__ v, int64_t rows, int64_t K,
     int64_t grp = blockIdx.x;
     load(a, grp);
     if constexpr (GELU) {
-        for (int i = threadIdx.x; i < (int)(sizeof(GeluTable) / 16); i += reg_block_threads<TPR>())
-            reinterpret_cast<float4 *>(gelu)[i] = reinterpret_cast<const float4 *>(&kGeluTable)[i];
+        // All of a thread's share of the table is requested before any of it is stored.
+        constexpr int N4 = sizeof(GeluTable) / 16, PER = (N4 + BS - 1) / BS;
+        float4 h[PER];
+#pragma unroll
+        for (int i = 0; i < PER; ++i)
+            h[i] = reinterpret_cast<const float4 *>(&kGeluTable)[min(i * BS + (int)threadIdx.x, N4 - 1)];
+#pragma unroll
+        for (int i = 0; i < PER; ++i)
+            if (i * BS + (int)threadIdx.x < N4)
+                reinterpret_cast<float4 *>(gelu)[i * BS + threadIdx.x] = h[i];
         __syncthreads();
     }
-    for (; grp < groups; grp += 2 * (int64_t)gridDim.x) {
-        load(b, grp + gridDim.x);
-        process(a, grp);
+    // The last row group is processed outside the loop, so that inside it every load and
+    // store is unconditional.
+    for (;;) {
         if (grp + gridDim.x >= groups)
             break;
-        load(a, grp + 2 * (int64_t)gridDim.x);
-        process(b, grp + gridDim.x);
+        load(b, grp + gridDim.x);
+        __builtin_amdgcn_sched_barrier(0);
+        process(a, grp);
+        grp += gridDim.x;
+        if (grp + gridDim.x >= groups) {
+#pragma unroll
+            for (int j = 0; j < NV; ++j)
+                a[j] = b[j];
+            break;
+        }
+        load(a, grp + gridDim.x);
+        __builtin_amdgcn_sched_barrier(0);
+        process(b, grp);
+        grp += gridDim.x;
     }
+    process(a, grp);
 }
 
 // General path: a 256-thread block per row (a block takes every G-th row when there are
@@ -538,28 +584,30 @@ hipError_t launch_rows(const uint16_t *v, int64_t rows, int64_t K, const float *
             if (nvec <= 1024)
                 return rows >= 4096 ? launch_reg<128, 8, ACT, CM>(v, rows, K, colmul, q, scale, s)
                                     : launch_reg<256, 4, ACT, CM>(v, rows, K, colmul, q, scale, s);
-            // Few long rows (K > 8192 below 256 rows): 512 threads per row, 5-9% faster
-            // than the 256-thread block.
-            if (rows < 256)
-                return nvec <= 1536 ? launch_reg<512, 3, ACT, CM>(v, rows, K, colmul, q, scale, s)
-                                    : launch_reg<512, 4, ACT, CM>(v, rows, K, colmul, q, scale, s);
+            // Long rows: 512 threads each while the rows are few (512 x 12288: 5.3 us, 5.8 on
+            // 256 x 6; 512 x 16384: 6.1, 6.6 on 256 x 8).
             if (nvec <= 1536)
-                return launch_reg<256, 6, ACT, CM>(v, rows, K, colmul, q, scale, s);
-            return rows >= 2048 ? launch_reg<1024, 2, ACT, CM>(v, rows, K, colmul, q, scale, s)
+                return rows < 1536 ? launch_reg<512, 3, ACT, CM>(v, rows, K, colmul, q, scale, s)
+                                   : launch_reg<256, 6, ACT, CM>(v, rows, K, colmul, q, scale, s);
+            if (rows < 768)
+                return launch_reg<512, 4, ACT, CM>(v, rows, K, colmul, q, scale, s);
+            return rows >= 4096 ? launch_reg<1024, 2, ACT, CM>(v, rows, K, colmul, q, scale, s)
                                 : launch_reg<256, 8, ACT, CM>(v, rows, K, colmul, q, scale, s);
         }
     } else {
-        // Transformed rows hold the float32 row too, so more threads with fewer vectors
-        // each pay from K = 4096 up; GELU rows also spread the copy of the table to LDS
-        // over more threads (us, GELU with the multiplier: 4608 x 16384 52.0 on 512 x 4
-        // against 60.0 on 256 x 8, 8192 x 6144 34.8 on 256 x 3 against 41.7 on 128 x 6,
-        // 8192 x 3072 21.2 on 128 x 3 against 24.2 on 64 x 6, 8192 x 2048 13.6 on 128 x 2
-        // against 16.7 on 64 x 4; multiplier alone: 8192 x 8192 36.5 on 512 x 2 against
-        // 38.5 on 256 x 4, 4110 x 4608 12.5 on 256 x 3 against 12.9 on 128 x 5).
+        // Transformed rows hold the float32 row too, so more threads with fewer vectors each
+        // pay; GELU rows also spread the copy of the table to LDS over more threads (us, GELU:
+        // 128 x 2560 3.3 on 512 x 1 against 3.9 on 128 x 3, 4608 x 2560 10.9 against 12.2 on
+        // 256 x 2, 2048 x 4096 7.9 on 512 x 1 against 8.6 on 256 x 2, 2048 x 16384 22.1 on
+        // 1024 x 2 against 24.8 on 512 x 4; with the multiplier 4608 x 16384 49.4 on 512 x 4,
+        // 54.6 on 256 x 8, 57.6 on 1024 x 2; multiplier alone: 512 x 16384 6.5 on 512 x 4,
+        // 7.0 on 256 x 8, 4608 x 16384 43.0 on 256 x 8, 43.9 on 512 x 4).
         constexpr bool GELU = ACT == ACT_GELU;
         if (vec && nvec > 192 && nvec <= 2048 && (nvec > 256 || rows >= 1024)) {
             if (nvec <= 256)
                 return launch_reg<128, 2, ACT, CM>(v, rows, K, colmul, q, scale, s);
+            if (nvec <= 512 && rows < (nvec <= 384 ? 1024 : 4096))
+                return launch_reg<512, 1, ACT, CM>(v, rows, K, colmul, q, scale, s);
             if (GELU && nvec <= 384)
                 return launch_reg<128, 3, ACT, CM>(v, rows, K, colmul, q, scale, s);
             if (nvec <= 512)
@@ -570,7 +618,9 @@ hipError_t launch_rows(const uint16_t *v, int64_t rows, int64_t K, const float *
                 return launch_reg<512, 2, ACT, CM>(v, rows, K, colmul, q, scale, s);
             if (nvec <= 1536)
                 return launch_reg<512, 3, ACT, CM>(v, rows, K, colmul, q, scale, s);
-            if (GELU || rows < 256)
+            if (GELU && !CM && rows < 4096)
+                return launch_reg<1024, 2, ACT, CM>(v, rows, K, colmul, q, scale, s);
+            if (GELU || rows < 768)
                 return launch_reg<512, 4, ACT, CM>(v, rows, K, colmul, q, scale, s);
             return launch_reg<256, 8, ACT, CM>(v, rows, K, colmul, q, scale, s);
         }
