@@ -40,6 +40,7 @@ LIB_PATH = os.path.join(_HERE, "libw8a8.so")
 MAX_K = 133144
 
 _lib = None
+_fn = {}     # the library's functions by name, typed
 
 
 class W8A8Error(RuntimeError):
@@ -96,26 +97,41 @@ def load_library():
         f = getattr(lib, name)
         f.argtypes = args
         f.restype = res
+        _fn[name] = f
     _lib = lib
     return lib
 
 
 def _call(name: str, *args) -> None:
-    lib = load_library()
-    st = getattr(lib, name)(*args)
+    f = _fn.get(name)
+    if f is None:
+        load_library()
+        f = _fn[name]
+    st = f(*args)
     if st != 0:
-        raise W8A8Error(name, st, lib.w8a8_status_string(st).decode())
+        raise W8A8Error(name, st, load_library().w8a8_status_string(st).decode())
+
+
+def _launch(device: torch.device, name: str, *args) -> None:
+    """_call with `device` current and its current stream as the last argument. The device
+    is switched only where it is another one: a call's host time is what a small linear
+    costs."""
+    index = device.index
+    if index is not None and torch._C._cuda_getDevice() == index:
+        _call(name, *args, torch._C._cuda_getCurrentRawStream(index))
+    else:
+        with torch.cuda.device(device):
+            _call(name, *args, torch.cuda.current_stream(device).cuda_stream)
 
 
 def _ptr(t: torch.Tensor | None):
-    return None if t is None else ctypes.c_void_p(t.data_ptr())
-
-
-def _stream(device: torch.device):
-    return ctypes.c_void_p(torch.cuda.current_stream(device).cuda_stream)
+    return None if t is None else t.data_ptr()
 
 
 def _check(t: torch.Tensor, dtype: torch.dtype, ndim: int, name: str):
+    if isinstance(t, torch.Tensor) and t.dtype == dtype and t.dim() == ndim and t.is_cuda \
+            and t.is_contiguous():
+        return
     if not isinstance(t, torch.Tensor):
         raise TypeError(f"{name} must be a torch.Tensor")
     if t.dtype != dtype:
@@ -138,10 +154,12 @@ def _check_out(t, dtype: torch.dtype, shape: tuple, device, name: str = "out"):
         raise ValueError(f"{name} is on {t.device}, expected {device}")
 
 
-def _same_device(*ts):
-    devs = {t.device for t in ts if t is not None}
-    if len(devs) > 1:
-        raise ValueError(f"tensors on different devices: {devs}")
+def _same_device(first, *ts):
+    d = first.device
+    for t in ts:
+        if t is not None and t.device != d:
+            raise ValueError(f"tensors on different devices: "
+                             f"{ {u.device for u in (first, *ts) if u is not None} }")
 
 
 def version() -> str:
@@ -168,12 +186,20 @@ def default_tile(M: int, N: int, K: int) -> int:
     return int(load_library().w8a8_default_tile(M, N, K))
 
 
+def _size(name: str, *args) -> int:
+    f = _fn.get(name)
+    if f is None:
+        load_library()
+        f = _fn[name]
+    return f(*args)
+
+
 def gemm_workspace_bytes(M: int, N: int, K: int, tile: int = -1) -> int:
-    return int(load_library().w8a8_gemm_workspace_bytes_ex(M, N, K, int(tile)))
+    return _size("w8a8_gemm_workspace_bytes_ex", M, N, K, int(tile))
 
 
 def linear_workspace_bytes(M: int, N: int, K: int) -> int:
-    return int(load_library().w8a8_linear_workspace_bytes(M, N, K))
+    return _size("w8a8_linear_workspace_bytes", M, N, K)
 
 
 def linear_one_launch(M: int, N: int, K: int) -> bool:
@@ -210,9 +236,7 @@ def quantize_weight(w: torch.Tensor, *, col_mul=None):
     cm = _col_mul(col_mul, K, w.device)
     q = torch.empty((N, K), dtype=torch.int8, device=w.device)
     s = torch.empty((N,), dtype=torch.float32, device=w.device)
-    with torch.cuda.device(w.device):
-        _call("w8a8_quantize_weight_ex", _ptr(w), N, K, _ptr(cm), _ptr(q), _ptr(s),
-              _stream(w.device))
+    _launch(w.device, "w8a8_quantize_weight_ex", _ptr(w), N, K, _ptr(cm), _ptr(q), _ptr(s))
     return q, s
 
 
@@ -225,9 +249,7 @@ def quantize_act(x: torch.Tensor, *, act: str = "none", col_mul=None):
     cm = _col_mul(col_mul, K, x.device)
     q = torch.empty((M, K), dtype=torch.int8, device=x.device)
     s = torch.empty((M,), dtype=torch.float32, device=x.device)
-    with torch.cuda.device(x.device):
-        _call("w8a8_quantize_act_ex", _ptr(x), M, K, a, _ptr(cm), _ptr(q), _ptr(s),
-              _stream(x.device))
+    _launch(x.device, "w8a8_quantize_act_ex", _ptr(x), M, K, a, _ptr(cm), _ptr(q), _ptr(s))
     return q, s
 
 
@@ -244,9 +266,7 @@ def col_absmax(v: torch.Tensor, *, act: str = "none", out=None, accumulate: bool
     _check(out, torch.float32, 1, "out")
     if out.shape[0] != K:
         raise ValueError("out must be [K]")
-    with torch.cuda.device(v.device):
-        _call("w8a8_col_absmax", _ptr(v), R, K, a, _ptr(out), int(bool(accumulate)),
-              _stream(v.device))
+    _launch(v.device, "w8a8_col_absmax", _ptr(v), R, K, a, _ptr(out), int(bool(accumulate)))
     return out
 
 
@@ -260,9 +280,8 @@ def smooth_factors(x_amax: torch.Tensor, w_amax: torch.Tensor, alpha: float = 0.
     K = x_amax.shape[0]
     s = torch.empty_like(x_amax)
     si = torch.empty_like(x_amax)
-    with torch.cuda.device(x_amax.device):
-        _call("w8a8_smooth_factors", _ptr(x_amax), _ptr(w_amax), K, float(alpha), _ptr(s),
-              _ptr(si), _stream(x_amax.device))
+    _launch(x_amax.device, "w8a8_smooth_factors", _ptr(x_amax), _ptr(w_amax), K, float(alpha),
+            _ptr(s), _ptr(si))
     return s, si
 
 
@@ -306,9 +325,8 @@ def gemm(xq, x_scale, wq, w_scale, bias=None, *, tile: int = -1, out=None,
                     (lambda: int(load_library().w8a8_gemm_workspace_least_bytes(M, N, K)))
                     if tile == -1 else None)
     nws = 0 if ws is None else ws.numel() * ws.element_size()
-    with torch.cuda.device(xq.device):
-        _call("w8a8_gemm_ex", _ptr(xq), _ptr(x_scale), _ptr(wq), _ptr(w_scale), _ptr(bias),
-              _ptr(y), M, N, K, _ptr(ws), nws, int(tile), _stream(xq.device))
+    _launch(xq.device, "w8a8_gemm_ex", _ptr(xq), _ptr(x_scale), _ptr(wq), _ptr(w_scale), _ptr(bias),
+            _ptr(y), M, N, K, _ptr(ws), nws, int(tile))
     return y
 
 
@@ -321,7 +339,7 @@ def linear(x, wq, w_scale, bias=None, *, act: str = "none", col_mul=None, out=No
         raise TypeError("x must be a bf16 torch.Tensor")
     lead = x.shape[:-1]
     K = x.shape[-1]
-    x2 = x.reshape(lead.numel(), K)
+    x2 = x if x.dim() == 2 else x.reshape(lead.numel(), K)
     _check(x2, torch.bfloat16, 2, "x")
     _check(wq, torch.int8, 2, "wq")
     _check(w_scale, torch.float32, 1, "w_scale")
@@ -341,10 +359,9 @@ def linear(x, wq, w_scale, bias=None, *, act: str = "none", col_mul=None, out=No
         return y.reshape(*lead, N)
     ws = _workspace(linear_workspace_bytes(M, N, K), x.device, workspace,
                     lambda: int(load_library().w8a8_linear_workspace_least_bytes(M, N, K)))
-    with torch.cuda.device(x.device):
-        _call("w8a8_linear_ex", _ptr(x2), a, _ptr(cm), _ptr(wq), _ptr(w_scale), _ptr(bias),
-              _ptr(y), M, N, K, _ptr(ws), ws.numel() * ws.element_size(), _stream(x.device))
-    return y.reshape(*lead, N)
+    _launch(x.device, "w8a8_linear_ex", _ptr(x2), a, _ptr(cm), _ptr(wq), _ptr(w_scale), _ptr(bias),
+            _ptr(y), M, N, K, _ptr(ws), ws.numel() * ws.element_size())
+    return y if x.dim() == 2 else y.reshape(*lead, N)
 
 
 def gemm_acc_i32(xq, wq, *, tile: int = -1, out=None):
@@ -360,9 +377,7 @@ def gemm_acc_i32(xq, wq, *, tile: int = -1, out=None):
         _check_out(out, torch.int32, (M, N), xq.device)
     acc = out if out is not None else torch.empty((M, N), dtype=torch.int32,
                                                   device=xq.device)
-    with torch.cuda.device(xq.device):
-        _call("w8a8_gemm_acc_i32_ex", _ptr(xq), _ptr(wq), _ptr(acc), M, N, K, int(tile),
-              _stream(xq.device))
+    _launch(xq.device, "w8a8_gemm_acc_i32_ex", _ptr(xq), _ptr(wq), _ptr(acc), M, N, K, int(tile))
     return acc
 
 
@@ -390,9 +405,7 @@ def mfma_ceiling(xq, wq, iters: int, *, out=None):
     _check(sums, torch.int32, 1, "out")
     if sums.numel() < 1024:
         raise ValueError("out needs 1024 entries")
-    with torch.cuda.device(xq.device):
-        _call("w8a8_mfma_ceiling", _ptr(xq), _ptr(wq), M, N, K, int(iters), _ptr(sums),
-              _stream(xq.device))
+    _launch(xq.device, "w8a8_mfma_ceiling", _ptr(xq), _ptr(wq), M, N, K, int(iters), _ptr(sums))
     return sums
 
 
@@ -412,6 +425,5 @@ def read_ceiling(buf: torch.Tensor, *, out=None):
     _check(sums, torch.int32, 1, "out")
     if sums.numel() < READ_BLOCKS or sums.device != buf.device:
         raise ValueError(f"out needs {READ_BLOCKS} entries on buf's device")
-    with torch.cuda.device(buf.device):
-        _call("w8a8_read_ceiling", _ptr(buf), nbytes, _ptr(sums), _stream(buf.device))
+    _launch(buf.device, "w8a8_read_ceiling", _ptr(buf), nbytes, _ptr(sums))
     return sums

@@ -92,8 +92,8 @@ class W8A8Linear(torch.nn.Module):
         return cls(wq, sw, b, act=act, smooth_inv=smooth_inv)
 
     def forward(self, x: torch.Tensor) -> torch.Tensor:
-        return torch.ops.w8a8.linear(x, self.wq, self.w_scale, self.bias, self.act,
-                                     self.smooth_inv)
+        return torch.ops.w8a8.linear.default(x, self.wq, self.w_scale, self.bias, self.act,
+                                             self.smooth_inv)
 
     def extra_repr(self) -> str:
         return (f"in_features={self.in_features}, out_features={self.out_features}, "
