@@ -18,8 +18,8 @@
 //     partials in a workspace, summed (exactly) by splitk_reduce_kernel, which also runs
 //     the epilogue.
 //   * gemm_i8_kernel: register-staged copies, for small tiles.
-//   * gemm_i8_any_kernel: operands that are not 16-byte aligned or whose K is not a
-//     multiple of 16, in 16-byte loads at the rows' own alignment.
+//   * gemm_i8_any_kernel: operands that are not 4-byte aligned or whose K is not a multiple
+//     of 4, in 16-byte loads at the rows' own alignment.
 //   * gemm_i8_skinny_kernel: few tokens (M <= 128). A workgroup streams 16*FNB weight
 //     rows once for all tokens with v_mfma_i32_16x16x64_i8, its wavefronts splitting K,
 //     partial sums reduced in LDS.
@@ -143,6 +143,7 @@ struct KParams {
     int k_split;     // workgroups per output tile along K (1: the whole K, direct epilogue)
     int k_chunk;     // K bytes per split (a multiple of BK; K when unsplit)
     int part_vec;    // partial rows 16-byte aligned (N % 4 == 0)
+    int dword;       // operands 4-byte aligned only: the DWORD kernels
     int32_t *part;   // k_split > 1: int32 partials [k_split][M][N]
     const uint16_t *x;   // the small fused linear: bf16 X [M,K] (a.xq, a.sx unused)
 };
@@ -498,7 +499,7 @@ __device__ __forceinline__ void barrier_nofence() {
     __builtin_amdgcn_sched_barrier(0);
 }
 
-// Operands at any alignment and any K (K % 16 != 0 or unaligned pointers): register-staged
+// Operands at any alignment and any K (K % 4 != 0 or such pointers): register-staged
 // copies like gemm_i8_kernel, but every 16-byte chunk is one global load at the row's own
 // alignment. Direct-to-LDS loads need dword-aligned addresses, so they are not used here.
 // Rows past M or N are read as the last row (their results are not stored); only the last
@@ -509,7 +510,7 @@ __device__ __forceinline__ void barrier_nofence() {
 // Bound by one panel's serial chain (register to LDS, barrier, fragment reads, MFMAs) and
 // the unaligned loads, each of which touches two cache lines: at 2001 x 1001 x 3001 it
 // takes 20.4 us, at K = 1008 15.0 us. Byte loads, which it replaces, took 129 us at
-// K = 1000 (now 17.0 us, 0.71 POP/s).
+// K = 1000 (17.0 us here; such a K now runs the direct-to-LDS tiles).
 template <int TM, int TN, int WM, int WN, int D, int EPI>
 __global__ void __launch_bounds__(WM *WN * 64)
 gemm_i8_any_kernel(KParams kp) {
@@ -700,7 +701,14 @@ gemm_i8_any_kernel(KParams kp) {
 //     the loads of panel k+S-1, one memory instruction between consecutive MFMAs.
 //   * Split-K (kp.k_split > 1): the workgroup covers one K-range of its tile and stores
 //     the int32 partial instead of running the epilogue.
-template <int TM, int TN, int BK, int WM, int WN, int S, int EPI>
+//   * DWORD: operands that are only 4-byte aligned, K % 4 == 0. The panel loads take any
+//     dword address (and drop dwords past the matrix one by one), so only the 16-byte chunk
+//     that crosses a row's end differs: it also brings the next row's first bytes. In the
+//     token part of the last panel these are set to zero in LDS, with a barrier of their own,
+//     before the panel is read; what they meet in the weight part does not matter then.
+//     2001 x 1000 x 3001: 15.9 us, against 17.9 on the any-alignment kernel (67 random
+//     shapes with K % 4 == 0: 1.2x in the geometric mean, 0.96 to 4.9).
+template <int TM, int TN, int BK, int WM, int WN, int S, int EPI, bool DWORD = false>
 __global__ void __launch_bounds__(WM *WN * 64)
 gemm_i8_lds_kernel(KParams kp) {
     constexpr int NW = WM * WN;                // wavefronts
@@ -936,6 +944,22 @@ gemm_i8_lds_kernel(KParams kp) {
         }
     };
 
+    // DWORD: the last panel's stage is at byte offset so and has landed for every wavefront.
+    auto clear_tail = [&](int so) {
+        const int last = KL - (nk - 1) * BK, from = last & 15;
+        if (from == 0)
+            return;
+        for (int r = (int)threadIdx.x; r < TM; r += NT) {
+            int32_t *c = reinterpret_cast<int32_t *>(smem + so + TN * BK + r * BK +
+                                                     (((last >> 4) ^ swz<BK>(r)) << 4));
+            for (int d = from >> 2; d < 4; ++d)
+                c[d] = 0;
+        }
+        __builtin_amdgcn_s_waitcnt(0xC07F);   // lgkmcnt(0)
+        barrier_nofence();
+    };
+    static_assert(!DWORD || S >= 3, "the last panel is cleared at the barrier before its K-steps");
+
     if (nk > 0) {
         // Prologue: panels 0 .. S-2 into stages 0 .. S-2; wait for panel 0.
 #pragma unroll
@@ -947,6 +971,9 @@ gemm_i8_lds_kernel(KParams kp) {
         barrier_nofence();
         int st = 0;            // stage of panel kt
         int ld = S - 1;        // stage of panel kt + S - 1
+        if constexpr (DWORD)
+            if (nk == 1)
+                clear_tail(0);
         if constexpr (EARLY) {
             read_frags(0, 0, 0);
             __builtin_amdgcn_sched_barrier(0);
@@ -964,6 +991,9 @@ gemm_i8_lds_kernel(KParams kp) {
                 wait_loads_mid();
                 __builtin_amdgcn_s_waitcnt(0xC07F);   // lgkmcnt(0)
                 barrier_nofence();
+                if constexpr (DWORD)
+                    if (kt + 2 == nk)
+                        clear_tail(nx * STAGE);
                 kstep(std::integral_constant<int, KS - 1>{}, st * STAGE, kt + S - 1,
                       ld * STAGE, nx * STAGE);
             } else {
@@ -1497,13 +1527,23 @@ struct Tile {
     // S >= 2: pipelined direct-to-LDS kernel with S stages; S == 0: the simple
     // register-staged kernel only.
     static constexpr bool PIPE = S >= 2;
+    static constexpr bool DWORD = S >= 3;      // takes 4-byte aligned operands too
     static constexpr int threads = WM * WN * 64;
     static constexpr int lds = (PIPE ? S : 2) * (TM + TN) * BK;
 
-    // Aligned operands only (16-byte pointers, K % 16 == 0); launch_gemm sends the rest
-    // to the generic tile.
+    // Aligned operands (16-byte pointers, K % 16 == 0), or with kp.dword 4-byte ones; the
+    // rest goes to the any-alignment kernels (launch_gemm).
     static hipError_t launch(Epilogue epi, const KParams &kp, hipStream_t s) {
         const dim3 grid((unsigned)(kp.tiles_m * kp.tiles_n * kp.k_split)), block(threads);
+        if constexpr (DWORD) {
+            if (kp.dword) {
+                if (epi == EPI_BF16)
+                    hipLaunchKernelGGL((gemm_i8_lds_kernel<TM, TN, BK, WM, WN, S, EPI_BF16, true>), grid, block, 0, s, kp);
+                else
+                    hipLaunchKernelGGL((gemm_i8_lds_kernel<TM, TN, BK, WM, WN, S, EPI_I32, true>), grid, block, 0, s, kp);
+                return hipGetLastError();
+            }
+        }
         if constexpr (PIPE) {
             if (epi == EPI_BF16)
                 hipLaunchKernelGGL((gemm_i8_lds_kernel<TM, TN, BK, WM, WN, S, EPI_BF16>), grid, block, 0, s, kp);
@@ -1586,7 +1626,7 @@ struct WsxTile {
     }
 };
 
-// Unaligned operands or K % 16 != 0.
+// Operands that are not 4-byte aligned or K % 4 != 0 (K % 16 != 0 up to 32 tokens).
 template <int TM, int TN, int WM, int WN, int D>
 hipError_t launch_any_tile(Epilogue epi, KParams &kp, hipStream_t s) {
     kp.tiles_m = (int)((kp.a.M + TM - 1) / TM);
@@ -1647,7 +1687,7 @@ struct TileEntry {
 #define W8A8_TILE(NAME, TM, TN, BK, WM, WN, GM, S)                                          \
     TileEntry {                                                                              \
         {NAME, TM, TN, BK, Tile<TM, TN, BK, WM, WN, S>::threads,                            \
-         Tile<TM, TN, BK, WM, WN, S>::lds, 1, -1, 0, S >= 2},                                        \
+         Tile<TM, TN, BK, WM, WN, S>::lds, 1, -1, 0, S >= 2, S >= 3},                                        \
             GM, &Tile<TM, TN, BK, WM, WN, S>::launch                                         \
     }
 
@@ -1655,20 +1695,20 @@ struct TileEntry {
 #define W8A8_TILE_SPLIT(NAME, TM, TN, BK, WM, WN, GM, S, KSPLIT, BASE)                    \
     TileEntry {                                                                              \
         {NAME, TM, TN, BK, Tile<TM, TN, BK, WM, WN, S>::threads,                            \
-         Tile<TM, TN, BK, WM, WN, S>::lds, KSPLIT, BASE, 0, true},                                 \
+         Tile<TM, TN, BK, WM, WN, S>::lds, KSPLIT, BASE, 0, true, S >= 3},                                 \
             GM, &Tile<TM, TN, BK, WM, WN, S>::launch                                         \
     }
 
 #define W8A8_SKINNY(NAME, FMB, FNB, NW)                                                  \
     TileEntry {                                                                              \
         {NAME, 16 * FMB, 16 * FNB, 256, SkinnyTile<FMB, FNB, NW>::threads,                  \
-         SkinnyTile<FMB, FNB, NW>::lds, 1, -1, 1, false},                                           \
+         SkinnyTile<FMB, FNB, NW>::lds, 1, -1, 1, false, false},                                           \
             1, &SkinnyTile<FMB, FNB, NW>::launch                                             \
     }
 
 #define W8A8_WSX(NAME, FMB, FNB, NW, D)                                                     \
     TileEntry {                                                                              \
-        {NAME, 16 * FMB, 16 * FNB, 128, WsxTile<FMB, FNB, NW, D>::threads, 0, 1, -1, 2, false},     \
+        {NAME, 16 * FMB, 16 * FNB, 128, WsxTile<FMB, FNB, NW, D>::threads, 0, 1, -1, 2, false, false},     \
             1, &WsxTile<FMB, FNB, NW, D>::launch                                             \
     }
 
@@ -1893,8 +1933,8 @@ static double stream_cost_us(const StreamCost &c, int64_t M, int64_t N, int64_t 
            1e-6 * (double)(wgs * K) * (c.w * t.tn + c.x * (double)rows);
 }
 
-// What runs a shape by default. Up to 16 tokens, and where the operands take the any-
-// alignment kernels, the selected tile. Above, the least predicted time over the tiles,
+// What runs a shape by default. Up to 16 tokens, and where K sends the operands to the any-
+// alignment kernels (K % 4 != 0, or K % 16 != 0 up to 32 tokens), the selected tile. Above, the least predicted time over the tiles,
 // each unsplit and with K split in as many ways as fit one round of workgroups; a table
 // entry stays unless the prediction beats its own clearly. On 1100 random shapes (M
 // 17..8192, N 128..20480, K 256..24576) the choice is within 1.8% of the fastest plan above
@@ -1905,7 +1945,8 @@ static double stream_cost_us(const StreamCost &c, int64_t M, int64_t N, int64_t 
 static GemmPlan compute_plan(int64_t M, int64_t N, int64_t K) {
     const int table = table_tile(M, N, K);
     GemmPlan best = tile_plan(table >= 0 ? table : fallback_tile(M, N, K));
-    if (M <= 16 || K < 16 || K % 16 != 0 || M > (1 << 20) || N > (1 << 20))
+    const bool aligned = K % 16 == 0;
+    if (M <= (aligned ? 16 : 32) || K < 16 || K % 4 != 0 || M > (1 << 20) || N > (1 << 20))
         return best;
     const uint32_t m = (uint32_t)M, n = (uint32_t)N, k = (uint32_t)K;
     const double mn = (double)M * (double)N;
@@ -1926,13 +1967,13 @@ static GemmPlan compute_plan(int64_t M, int64_t N, int64_t K) {
             best = GemmPlan{id, (int)splits};
         }
     };
-    if (M <= 128)
+    if (M <= 128 && aligned)
         for (const StreamCost &c : kStreamCost)
             consider(c.tile, 1, stream_cost_us(c, M, N, K));
     const uint32_t by_space = (uint32_t)(kSplitWorkspace / 4 / (mn > 1.0 ? mn : 1.0));
     for (int id = 0; id < kNumTiles; ++id) {
         const TileInfo &t = kTiles[id].info;
-        if (t.base >= 0 || !(kTileCost[id].d > 0.0))
+        if (t.base >= 0 || !(kTileCost[id].d > 0.0) || !(aligned || t.dword))
             continue;
         const uint32_t tiles = tiles_of(t);
         consider(id, 1, plan_cost_us(id, tiles, 1, mn, k));
@@ -1940,7 +1981,7 @@ static GemmPlan compute_plan(int64_t M, int64_t N, int64_t K) {
     const double unsplit = table >= 0 ? limit / kOverTable : limit;
     for (int id = 0; id < kNumTiles && unsplit > kSplitWorthUs; ++id) {
         const TileInfo &t = kTiles[id].info;
-        if (t.base >= 0 || !t.splittable || !(kTileCost[id].d > 0.0))
+        if (t.base >= 0 || !t.splittable || !(kTileCost[id].d > 0.0) || !(aligned || t.dword))
             continue;
         const uint32_t tiles = tiles_of(t);
         if (tiles > 128)
@@ -2046,6 +2087,7 @@ hipError_t launch_linear_small(const uint16_t *x, const int8_t *wq, const float 
     kp.k_chunk = (int)K;
     kp.part = nullptr;
     kp.part_vec = 0;
+    kp.dword = 0;
     kp.x = x;
     return t.launch(EPI_BF16, kp, stream);
 }
@@ -2072,9 +2114,17 @@ hipError_t launch_gemm(const GemmPlan &plan, Epilogue epi, bool vec, const GemmA
     kp.k_chunk = (int)a.K;
     kp.part = nullptr;
     kp.part_vec = 0;
+    kp.dword = 0;
     kp.x = nullptr;
-    if (!vec)
-        return launch_any(epi, kp, stream);
+    if (!vec) {
+        // Up to 32 tokens the any-alignment kernels stream the weight.
+        const bool dword = a.K % 4 == 0 && a.M > 32 && t.info.dword &&
+                           (reinterpret_cast<uintptr_t>(a.xq) |
+                            reinterpret_cast<uintptr_t>(a.wq)) % 4 == 0;
+        if (!dword)
+            return launch_any(epi, kp, stream);
+        kp.dword = 1;
+    }
     if (plan.splits > 1) {
         int chunk = 0;
         const int splits = split_count(t.info, plan.splits, a.K, &chunk);

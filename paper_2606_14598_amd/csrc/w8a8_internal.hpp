@@ -46,6 +46,7 @@ struct TileInfo {
     int base;            // for a split tile, the id of the same tile unsplit (else -1)
     int streaming;       // 1, 2: a weight-streaming kernel for few tokens
     bool splittable;     // its kernel can divide K among workgroups
+    bool dword;          // and takes operands that are only 4-byte aligned
 };
 
 // A tile with K divided among `splits` workgroups per output tile.
