@@ -23,6 +23,7 @@
 //   * gemm_i8_skinny_kernel: few tokens (M <= 128). A workgroup streams 16*FNB weight
 //     rows once for all tokens with v_mfma_i32_16x16x64_i8, its wavefronts splitting K,
 //     partial sums reduced in LDS.
+//   * gemv_i8_kernel: up to 8 tokens, dot4 on whole weight rows.
 //   * gemm_i8_wsx_kernel: few tokens, in blocks of 16 or 32. The same product with the
 //     token block staged once per workgroup in LDS and the weight streamed through a
 //     register ring; it also quantizes the bf16 token rows itself for the one-launch
@@ -1461,6 +1462,137 @@ gemm_i8_wsx_kernel(KParams kp) {
     }
 }
 
+// Up to 8 tokens: y[m][n] = W[n] . x[m], bound by reading W. Unlike the matrix instructions'
+// fragments (16 rows x 64 bytes an instruction), dot4 lets a wavefront read whole rows: 1 KB
+// of one row per load, eight loads in flight per lane, the order in which a plain read of W is
+// fastest. A wavefront takes R = 8 / J rows and J KB of each per turn; the MT tokens' codes lie
+// in LDS and are read once for all its rows. With QX (one token) every workgroup quantizes the
+// bf16 token itself, with the row quantizer's arithmetic, while its weight loads are in flight:
+// XV 16-byte loads a thread hold it. Without, the codes go to LDS directly.
+// 1 x 4096 x 16384 with QX takes 13.4 us (5.0 TB/s; a plain read of as many bytes 12.1 us, the
+// matrix-instruction kernel 17.6 us), 1 x 4096 x 4096 4.9 us (6.7), 1 x 8192 x 128 3.0 (7.4).
+template <int J, int MT, bool QX, int XV = 4>
+__global__ void __launch_bounds__(256) gemv_i8_kernel(KParams kp) {
+    static_assert(MT == 1 || !QX, "one token is quantized here");
+    constexpr int R = 8 / J;                   // rows per wavefront
+    constexpr int CH = 1024 * J;               // bytes of a row per turn
+    const GemmArgs &a = kp.a;
+    const int t = threadIdx.x, lane = t & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
+    const int M = (int)a.M, K = (int)a.K;
+    const int64_t N = a.N, n0 = ((int64_t)blockIdx.x * 4 + wave) * R;
+    const int rows = n0 >= N ? 0 : (int)(N - n0 < R ? N - n0 : R);
+    const int64_t nb = rows > 0 ? n0 : 0;      // a wavefront past N reads and stores nothing
+    const int turns = (K + CH - 1) / CH, padded = turns * CH;
+    // Codes, token rows of `padded` bytes with zeros from K on; behind them 4 row maxima.
+    extern __shared__ __attribute__((aligned(1024))) int8_t gemv_lds[];
+    int8_t *const xs = gemv_lds;
+    uint32_t *const pmax = reinterpret_cast<uint32_t *>(gemv_lds + MT * padded);
+
+    // The tokens and this wavefront's scales first, so that the wait for them leaves the
+    // weight loads in flight. Lane l ends with output (row l / MT, token l % MT).
+    const __amdgpu_buffer_rsrc_t rx = __builtin_amdgcn_make_buffer_rsrc(
+        QX ? (void *)kp.x : (void *)a.xq, (short)0, QX ? 2 * K : M * K, kRsrcWord3);
+    u32x4 xv[QX ? XV : 1];
+    if constexpr (QX) {
+#pragma unroll
+        for (int i = 0; i < XV; ++i)
+            xv[i] = __builtin_amdgcn_raw_buffer_load_b128(rx, (i * 256 + t) * 16, 0, 0);
+    } else {
+        const int segs = padded >> 10;         // kilobytes per token row
+        for (int g = wave; g < MT * segs; g += 4) {
+            const int m = g / segs, k = (g - m * segs) * 1024 + lane * 16;
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(
+                rx, (__attribute__((address_space(3))) void *)(xs + g * 1024), 16,
+                m < M && k < K ? m * K + k : kOOB, 0, 0, 0);
+        }
+    }
+    const int om = lane % MT, orow = lane / MT;
+    const bool out = orow < rows && om < M;
+    const int64_t on = nb + (out ? orow : 0);
+    const float swn = a.sw[on];
+    const float bn = a.bias ? __uint_as_float((uint32_t)a.bias[on] << 16) : 0.0f;
+    float sx = QX ? 0.0f : a.sx[out ? om : 0];
+    __builtin_amdgcn_sched_barrier(0);
+
+    const __amdgpu_buffer_rsrc_t rw = __builtin_amdgcn_make_buffer_rsrc(
+        (void *)(a.wq + nb * K), (short)0, rows * K, kRsrcWord3);
+    u32x4 wv[R][J];
+    auto load = [&](int r, int j, int c) __attribute__((always_inline)) {
+        const int k = c * CH + j * 1024 + lane * 16;
+        wv[r][j] = __builtin_amdgcn_raw_buffer_load_b128(rw, k < K ? r * K + k : kOOB, 0, 0);
+    };
+#pragma unroll
+    for (int j = 0; j < J; ++j)
+#pragma unroll
+        for (int r = 0; r < R; ++r)
+            load(r, j, 0);
+    __builtin_amdgcn_sched_barrier(0);
+
+    const auto sync = [&]() {
+        __builtin_amdgcn_s_waitcnt(0xC07F);    // lgkmcnt(0)
+        barrier_nofence();
+    };
+    if constexpr (QX) {
+        uint32_t m = 0;
+#pragma unroll
+        for (int i = 0; i < XV; ++i)
+            m = max(m, qmath::absmax8(make_uint4(xv[i].x, xv[i].y, xv[i].z, xv[i].w)));
+        m = qmath::wave_max(m);
+        if (lane == 0)
+            pmax[wave] = m;
+        sync();
+        const qmath::RowScale rs =
+            qmath::row_scale(max(max(pmax[0], pmax[1]), max(pmax[2], pmax[3])));
+        sx = rs.scale;
+#pragma unroll
+        for (int i = 0; i < XV; ++i)
+            if ((i * 256 + t) * 8 < padded)
+                *reinterpret_cast<uint2 *>(xs + (i * 256 + t) * 8) =
+                    qmath::code8(make_uint4(xv[i].x, xv[i].y, xv[i].z, xv[i].w), rs.inv);
+    } else {
+        __builtin_amdgcn_s_waitcnt(waitcnt_vm(8));   // all but the weight loads have landed
+    }
+    sync();
+
+    int acc[R][MT] = {};
+    auto turn = [&](int c, auto more) __attribute__((always_inline)) {
+#pragma unroll
+        for (int j = 0; j < J; ++j) {
+            i32x4 x[MT];
+#pragma unroll
+            for (int m = 0; m < MT; ++m)
+                x[m] = *reinterpret_cast<const i32x4 *>(xs + m * padded + c * CH + j * 1024 + lane * 16);
+#pragma unroll
+            for (int r = 0; r < R; ++r) {
+#pragma unroll
+                for (int m = 0; m < MT; ++m)
+#pragma unroll
+                    for (int e = 0; e < 4; ++e)
+                        acc[r][m] = __builtin_amdgcn_sdot4((int)wv[r][j][e], x[m][e], acc[r][m], false);
+                if constexpr (decltype(more)::value)
+                    load(r, j, c + 1);
+            }
+        }
+    };
+    for (int c = 0; c + 1 < turns; ++c)
+        turn(c, std::integral_constant<bool, true>{});
+    turn(turns - 1, std::integral_constant<bool, false>{});
+
+    int mine = 0;
+#pragma unroll
+    for (int r = 0; r < R; ++r)
+#pragma unroll
+        for (int m = 0; m < MT; ++m) {
+            const int sum = qmath::wave_sum(acc[r][m]);
+            mine = lane == r * MT + m ? sum : mine;
+        }
+    if (out) {
+        const float y = __builtin_fmaf((float)mine, sx * swn, bn);
+        static_cast<uint16_t *>(a.out)[om * N + on] = __builtin_bit_cast(uint16_t, (__bf16)y);
+    }
+}
+
 // ---------------------------------------------------------------- tile registry
 
 // Split-K reduction and epilogue: acc = sum of the k_split int32 partials (exact in any
@@ -1625,6 +1757,57 @@ struct WsxTile {
                                : go<EPI_I32, false>(kp, (size_t)dyn, s);
     }
 };
+
+// Up to 8 tokens: the row-reading kernel, as long as the tokens' codes leave room for five
+// workgroups per CU (32 KB); the token it quantizes itself has at most 16384 values (eight
+// 16-byte loads a thread). Against the streaming tiles' GEMM, over 30 shapes each: 1.2-2.9x
+// for one token, 1.1-2.6x for two, 1.05-2.0x for up to four. With more tokens the sums'
+// reduction shows, and only weights of 32 MB and more gain (7 tokens: 18432 x 3072 20.0 -> 16.0
+// us, 16384 x 4096 18.0 -> 16.2; but 5072 x 480 4.7 -> 5.3).
+constexpr int64_t kGemvLds = 32 << 10;
+constexpr int64_t kGemvManyTokens = 32 << 20;
+
+int gemv_j(int64_t K) { return K <= 2048 ? 2 : K <= 4096 ? 4 : 8; }
+
+int64_t gemv_code_bytes(int64_t M, int64_t K) {
+    const int64_t ch = 1024 * gemv_j(K), mt = M <= 1 ? 1 : M <= 2 ? 2 : M <= 4 ? 4 : 8;
+    return mt * ((K + ch - 1) / ch * ch);
+}
+
+bool gemv_shape(int64_t M, int64_t N, int64_t K, bool quantize) {
+    if (M < 1 || M > (quantize ? 1 : 8) || K < 16 || K % 16 != 0 || N > (int64_t)1 << 31)
+        return false;
+    if (M > 4 && N * K < kGemvManyTokens)
+        return false;
+    return quantize ? K <= 16384 : gemv_code_bytes(M, K) <= kGemvLds;
+}
+
+template <int J>
+void launch_gemv_j(const KParams &kp, hipStream_t s) {
+    const dim3 grid((unsigned)((kp.a.N + 32 / J - 1) / (32 / J))), block(256);
+    const size_t lds = (size_t)gemv_code_bytes(kp.a.M, kp.a.K) + 16;
+    if (kp.x && kp.a.K <= 8192)
+        hipLaunchKernelGGL((gemv_i8_kernel<J, 1, true>), grid, block, lds, s, kp);
+    else if (kp.x)
+        hipLaunchKernelGGL((gemv_i8_kernel<8, 1, true, 8>), grid, block, lds, s, kp);
+    else if (kp.a.M == 1)
+        hipLaunchKernelGGL((gemv_i8_kernel<J, 1, false>), grid, block, lds, s, kp);
+    else if (kp.a.M == 2)
+        hipLaunchKernelGGL((gemv_i8_kernel<J, 2, false>), grid, block, lds, s, kp);
+    else if (kp.a.M <= 4)
+        hipLaunchKernelGGL((gemv_i8_kernel<J, 4, false>), grid, block, lds, s, kp);
+    else if constexpr (J < 8)              // eight token rows past 4096 exceed kGemvLds
+        hipLaunchKernelGGL((gemv_i8_kernel<J, 8, false>), grid, block, lds, s, kp);
+}
+
+hipError_t launch_gemv(const KParams &kp, hipStream_t s) {
+    switch (gemv_j(kp.a.K)) {
+    case 2: launch_gemv_j<2>(kp, s); break;
+    case 4: launch_gemv_j<4>(kp, s); break;
+    default: launch_gemv_j<8>(kp, s); break;
+    }
+    return hipGetLastError();
+}
 
 // Operands that are not 4-byte aligned or K % 4 != 0 (K % 16 != 0 up to 32 tokens).
 template <int TM, int TN, int WM, int WN, int D>
@@ -1897,7 +2080,7 @@ static int split_count(const TileInfo &t, int splits, int64_t K, int *chunk) {
 }
 
 GemmPlan tile_plan(int id) {
-    return GemmPlan{id, id >= 0 && id < kNumTiles ? kTiles[id].info.ksplit : 1};
+    return GemmPlan{id, id >= 0 && id < kNumTiles ? kTiles[id].info.ksplit : 1, false};
 }
 
 size_t plan_workspace_bytes(const GemmPlan &p, int64_t M, int64_t N, int64_t K) {
@@ -1964,7 +2147,7 @@ static GemmPlan compute_plan(int64_t M, int64_t N, int64_t K) {
     const auto consider = [&](int id, uint32_t splits, double us) {
         if (limit < 0.0 || us < limit) {
             limit = us;
-            best = GemmPlan{id, (int)splits};
+            best = GemmPlan{id, (int)splits, false};
         }
     };
     if (M <= 128 && aligned)
@@ -2012,7 +2195,9 @@ GemmPlan select_plan(int64_t M, int64_t N, int64_t K) {
     Entry &e = kept[h >> 58];
     if (e.m != M || e.n != N || e.k != K)
         e = Entry{M, N, K, compute_plan(M, N, K)};
-    return e.plan;
+    GemmPlan p = e.plan;
+    p.chosen = true;
+    return p;
 }
 
 // LDS of one workgroup on gfx950.
@@ -2089,6 +2274,8 @@ hipError_t launch_linear_small(const uint16_t *x, const int8_t *wq, const float 
     kp.part_vec = 0;
     kp.dword = 0;
     kp.x = x;
+    if (gemv_shape(M, N, K, true))
+        return launch_gemv(kp, stream);
     return t.launch(EPI_BF16, kp, stream);
 }
 
@@ -2124,6 +2311,8 @@ hipError_t launch_gemm(const GemmPlan &plan, Epilogue epi, bool vec, const GemmA
         if (!dword)
             return launch_any(epi, kp, stream);
         kp.dword = 1;
+    } else if (plan.chosen && epi == EPI_BF16 && gemv_shape(a.M, a.N, a.K, false)) {
+        return launch_gemv(kp, stream);
     }
     if (plan.splits > 1) {
         int chunk = 0;

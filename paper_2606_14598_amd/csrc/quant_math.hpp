@@ -55,6 +55,20 @@ __device__ __forceinline__ uint32_t wave_max(uint32_t v) {
     return (uint32_t)__builtin_amdgcn_readlane((int)v, 63);
 }
 
+// Sum over the wavefront, by the same steps.
+__device__ __forceinline__ int wave_sum(int v) {
+    const auto step = [&](auto ctrl) {
+        v += __builtin_amdgcn_update_dpp(0, v, decltype(ctrl)::value, 0xF, 0xF, true);
+    };
+    step(std::integral_constant<int, 0x111>{});   // row_shr:1
+    step(std::integral_constant<int, 0x112>{});   // row_shr:2
+    step(std::integral_constant<int, 0x114>{});   // row_shr:4
+    step(std::integral_constant<int, 0x118>{});   // row_shr:8
+    v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xA, 0xF, true);   // row_bcast:15, rows 1, 3
+    v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xC, 0xF, true);   // row_bcast:31, rows 2, 3
+    return __builtin_amdgcn_readlane(v, 63);
+}
+
 // Codes of four values: clamp(rne(v * inv), -127, 127) as bytes, the first lowest. The
 // product is clamped (the same as clamping its rounding: the bounds are integers) and
 // 1.5 * 2^23 added, which rounds it to the nearest even integer and leaves the code in

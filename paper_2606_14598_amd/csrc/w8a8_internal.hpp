@@ -52,6 +52,7 @@ struct TileInfo {
 // A tile with K divided among `splits` workgroups per output tile.
 struct GemmPlan {
     int tile, splits;
+    bool chosen;         // by the library's rules (a given tile id runs as it is)
 };
 
 int tile_count();
