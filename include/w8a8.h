@@ -88,7 +88,7 @@ size_t w8a8_gemm_workspace_bytes(int64_t M, int64_t N, int64_t K);
  * less far or not at all, at the speed that leaves. */
 size_t w8a8_gemm_workspace_least_bytes(int64_t M, int64_t N, int64_t K);
 
-/* Workspace of w8a8_gemm_ex with a given tile id (-1: the table's choice). Tiles that
+/* Workspace of w8a8_gemm_ex with a given tile id (-1: the library's choice). Tiles that
  * split K among several workgroups per output tile keep int32 partial products
  * [splits][M][N] there; the others need none (0). */
 size_t w8a8_gemm_workspace_bytes_ex(int64_t M, int64_t N, int64_t K, int tile_id);
@@ -147,7 +147,9 @@ w8a8_status w8a8_gemm_acc_i32(const int8_t *xq, const int8_t *wq, int32_t *acc,
  * shape (M within an entry's token range, N and K equal), else the fallback rule's;
  * w8a8_default_tile returns the fallback rule's choice alone, the untuned arm of the
  * tuning ablation. Both return -1 for M <= 0, N <= 0 or K < 0. The _ex variants run a
- * given id (-1 = the table's choice) for offline sweeps and tests. An id outside
+ * given id for offline sweeps and tests; -1 lets the library choose: the selected id, or
+ * for up to 8 tokens a kernel of its own, or above 16 tokens the tile and K split that its
+ * cost model prefers. An id outside
  * [0, w8a8_tile_count()) returns W8A8_ERR_ARG. Tiles whose name ends in _k<s> divide K
  * among s workgroups per output tile and sum the int32 partials in a second kernel (the
  * result is the same: integer sums are exact); w8a8_gemm_acc_i32[_ex] runs them
