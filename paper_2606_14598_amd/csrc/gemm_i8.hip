@@ -2123,7 +2123,7 @@ static double stream_cost_us(const StreamCost &c, int64_t M, int64_t N, int64_t 
 // 17..8192, N 128..20480, K 256..24576) the choice is within 1.8% of the fastest plan above
 // 128 tokens (geometric mean; 5% below 32, 3.4% up to 64, 1.5% up to 128), where the table's
 // fallback was 22% off (12, 16 and 28%): long K on few output tiles left most CUs idle
-// (512 x 4608 x 53248: 162.7 us split in two, 137.9 in three on 216 workgroups), and tiles
+// (512 x 4608 x 53248: 162.7 us split in two, 138.8 in seven on 252 workgroups), and tiles
 // without a deep ring were taken for small outputs (640 x 1024 x 4096: 20.7 against 11.0 us).
 static GemmPlan compute_plan(int64_t M, int64_t N, int64_t K) {
     const int table = table_tile(M, N, K);
