@@ -2083,8 +2083,13 @@ GemmPlan tile_plan(int id) {
     return GemmPlan{id, id >= 0 && id < kNumTiles ? kTiles[id].info.ksplit : 1, false};
 }
 
+// Sizes that only the any-alignment kernels run (launch_gemm), whatever the plan's tile.
+static bool any_alignment_only(int64_t M, int64_t K) {
+    return K % 4 != 0 || (K % 16 != 0 && M <= 32);
+}
+
 size_t plan_workspace_bytes(const GemmPlan &p, int64_t M, int64_t N, int64_t K) {
-    if (p.tile < 0 || p.tile >= kNumTiles || p.splits <= 1)
+    if (p.tile < 0 || p.tile >= kNumTiles || p.splits <= 1 || any_alignment_only(M, K))
         return 0;
     const int splits = split_count(kTiles[p.tile].info, p.splits, K, nullptr);
     return splits > 1 ? (size_t)splits * (size_t)M * (size_t)N * sizeof(int32_t) : 0;
@@ -2116,8 +2121,8 @@ static double stream_cost_us(const StreamCost &c, int64_t M, int64_t N, int64_t 
            1e-6 * (double)(wgs * K) * (c.w * t.tn + c.x * (double)rows);
 }
 
-// What runs a shape by default. Up to 16 tokens, and where K sends the operands to the any-
-// alignment kernels (K % 4 != 0, or K % 16 != 0 up to 32 tokens), the selected tile. Above, the least predicted time over the tiles,
+// What runs a shape by default. Up to 16 tokens, and where K sends the operands to the
+// any-alignment kernels, the selected tile. Above, the least predicted time over the tiles,
 // each unsplit and with K split in as many ways as fit one round of workgroups; a table
 // entry stays unless the prediction beats its own clearly. On 1100 random shapes (M
 // 17..8192, N 128..20480, K 256..24576) the choice is within 1.8% of the fastest plan above
@@ -2129,7 +2134,7 @@ static GemmPlan compute_plan(int64_t M, int64_t N, int64_t K) {
     const int table = table_tile(M, N, K);
     GemmPlan best = tile_plan(table >= 0 ? table : fallback_tile(M, N, K));
     const bool aligned = K % 16 == 0;
-    if (M <= (aligned ? 16 : 32) || K < 16 || K % 4 != 0 || M > (1 << 20) || N > (1 << 20))
+    if (M <= 16 || K < 16 || any_alignment_only(M, K) || M > (1 << 20) || N > (1 << 20))
         return best;
     const uint32_t m = (uint32_t)M, n = (uint32_t)N, k = (uint32_t)K;
     const double mn = (double)M * (double)N;

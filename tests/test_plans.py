@@ -1,0 +1,53 @@
+"""The host side of the default plan: what it asks of the caller, and the rules of its cost
+model (no GPU needed, except where marked)."""
+import numpy as np
+import pytest
+
+import paper_2606_14598_amd as w8a8
+
+# Sizes that only the any-alignment kernels run: K % 4 != 0, or K % 16 != 0 up to 32 tokens.
+ANY_ALIGNMENT = [(64, 4096, 8193), (20, 4096, 8200), (100, 8000, 8193), (32, 2049, 16388),
+                 (33, 4096, 8194), (128, 100, 133143), (512, 4608, 53247), (1, 1, 1)]
+
+
+@pytest.mark.parametrize("M,N,K", ANY_ALIGNMENT)
+def test_any_alignment_sizes_need_no_partials(M, N, K):
+    """Those kernels never split K, so neither the query nor the least may ask for
+    partials, whichever tile is given."""
+    lib = w8a8.load_library()
+    for tile in range(-1, w8a8.tile_count()):
+        assert w8a8.gemm_workspace_bytes(M, N, K, tile) == 0, tile
+    assert lib.w8a8_gemm_workspace_least_bytes(M, N, K) == 0
+    head = -(-M * K // 256) * 256 + -(-4 * M // 256) * 256     # Xq and sx
+    assert w8a8.linear_workspace_bytes(M, N, K) == head
+    assert lib.w8a8_linear_workspace_least_bytes(M, N, K) == head
+
+
+def test_sizes_beside_them_keep_their_partials():
+    assert w8a8.gemm_workspace_bytes(64, 4096, 8192) > 0
+    assert w8a8.gemm_workspace_bytes(33, 640, 24572) > 0
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("M,N,K", [(64, 1000, 8193), (20, 4096, 8200)])
+def test_any_alignment_gemm_without_a_workspace(M, N, K):
+    import torch
+    import oracle
+    import synth_inputs as si
+    from _helpers import dev_bf16, host_bits, say
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    lib = w8a8.load_library()
+    say(f"no workspace M={M} N={N} K={K}")
+    x, w, b = si.make_inputs((M, K, N), seed=M + K)
+    wq_o, sw_o = oracle.quantize_rows(w)
+    y_o, xq_o, sx_o, _ = oracle.linear(x, wq_o, sw_o, b)
+    xq, sx = w8a8.quantize_act(dev_bf16(x))
+    wq, sw = w8a8.quantize_weight(dev_bf16(w))
+    bd = dev_bf16(b)
+    y = torch.empty(M, N, dtype=torch.bfloat16, device="cuda")
+    st = lib.w8a8_gemm(xq.data_ptr(), sx.data_ptr(), wq.data_ptr(), sw.data_ptr(),
+                       bd.data_ptr(), y.data_ptr(), M, N, K, None, 0,
+                       torch.cuda.current_stream().cuda_stream)
+    assert st == 0, lib.w8a8_status_string(st)
+    assert np.array_equal(host_bits(y), y_o)
