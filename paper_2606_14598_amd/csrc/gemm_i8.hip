@@ -2142,18 +2142,22 @@ static GemmPlan compute_plan(int64_t M, int64_t N, int64_t K) {
         return ((m + t.tm - 1) / (uint32_t)t.tm) * ((n + t.tn - 1) / (uint32_t)t.tn);
     };
     double limit = -1.0;               // none yet
+    double unsplit = -1.0;             // the best unsplit prediction so far
     if (table >= 0) {
         const TileInfo &bt = kTiles[table].info;
         const int base = bt.base >= 0 ? bt.base : table;
         if (!(kTileCost[base].d > 0.0))
             return best;
         limit = kOverTable * plan_cost_us(base, tiles_of(bt), best.splits, mn, k);
+        unsplit = plan_cost_us(base, tiles_of(bt), 1, mn, k);
     }
     const auto consider = [&](int id, uint32_t splits, double us) {
         if (limit < 0.0 || us < limit) {
             limit = us;
             best = GemmPlan{id, (int)splits, false};
         }
+        if (splits == 1 && (unsplit < 0.0 || us < unsplit))
+            unsplit = us;
     };
     if (M <= 128 && aligned)
         for (const StreamCost &c : kStreamCost)
@@ -2166,7 +2170,6 @@ static GemmPlan compute_plan(int64_t M, int64_t N, int64_t K) {
         const uint32_t tiles = tiles_of(t);
         consider(id, 1, plan_cost_us(id, tiles, 1, mn, k));
     }
-    const double unsplit = table >= 0 ? limit / kOverTable : limit;
     for (int id = 0; id < kNumTiles && unsplit > kSplitWorthUs; ++id) {
         const TileInfo &t = kTiles[id].info;
         if (t.base >= 0 || !t.splittable || !(kTileCost[id].d > 0.0) || !(aligned || t.dword))

@@ -1,5 +1,8 @@
 """The host side of the default plan: what it asks of the caller, and the rules of its cost
 model (no GPU needed, except where marked)."""
+import os
+import re
+
 import numpy as np
 import pytest
 
@@ -26,6 +29,41 @@ def test_any_alignment_sizes_need_no_partials(M, N, K):
 def test_sizes_beside_them_keep_their_partials():
     assert w8a8.gemm_workspace_bytes(64, 4096, 8192) > 0
     assert w8a8.gemm_workspace_bytes(33, 640, 24572) > 0
+
+
+def _tile_table():
+    """(costs by tile id, entries (m_lo, m_hi, N, K, tile)) of tile_table.inc."""
+    path = os.path.join(os.path.dirname(w8a8.__file__), "csrc", "tile_table.inc")
+    text = open(path).read()
+    costs = text[text.index("kTileCost[] = {"):]
+    costs = re.findall(r"\{([-0-9.e+]+), ([-0-9.e+]+)\}", costs[:costs.index("};")])
+    entries = re.findall(r"\{(\d+), (\d+), (\d+), (\d+), (\d+)\}", text)
+    return ([(float(c), float(d)) for c, d in costs], [tuple(map(int, e)) for e in entries])
+
+
+def test_k_is_split_only_where_the_best_unsplit_tile_takes_over_12_us():
+    """Over the table's shapes (above 128 tokens, where every unsplit candidate is in the
+    wave cost model) and random ones without an entry."""
+    costs, entries = _tile_table()
+    names = [w8a8.tile_name(i) for i in range(w8a8.tile_count())]
+    dims = [re.match(r"m(\d+)n(\d+)", n) for n in names]
+    dims = [m and (int(m[1]), int(m[2])) for m in dims]
+
+    def unsplit_us(M, N, K):
+        return min(1e3 * -(-(-(-M // tm) * -(-N // tn)) // 256) * (c + d * 1e-9 * tm * tn * K)
+                   for (c, d), (tm, tn) in ((costs[i], dims[i]) for i in range(len(names))
+                                            if costs[i][1] > 0))
+    rng = np.random.default_rng(5)
+    shapes = {(M, N, K) for lo, hi, N, K, _ in entries
+              for M in (lo, (lo + min(hi, 9000)) // 2, min(hi, 9000)) if 128 < M <= 9000}
+    shapes |= {(int(2 ** rng.uniform(7.1, 12)), int(2 ** rng.uniform(7, 13)),
+                int(2 ** rng.uniform(8, 14.6)) // 16 * 16) for _ in range(2000)}
+    split = 0
+    for M, N, K in sorted(shapes):
+        if w8a8.gemm_workspace_bytes(M, N, K) > 0:
+            split += 1
+            assert unsplit_us(M, N, K) > 12.0, (M, N, K)
+    assert split > 50
 
 
 @pytest.mark.gpu
