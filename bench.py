@@ -18,7 +18,7 @@ Prints one JSON line. Besides the required fields it carries:
                 taken on the current kernel source, else null; mfma_ceiling = what the
                 int8 matrix cores sustain on this GEMM's own codes (its MFMA sequence
                 replayed from registers), against which the GEMM's rate is also given
-  shapes        per linear: tile, GEMM and quantizer durations, and (full run) the whole
+  shapes        per linear: tile (with its K split), GEMM and quantizer durations, and (full run) the whole
                 linear with bf16 / fake-quant / unfused-int8 comparators
   comparators   the same comparators summed over one step
   config1_attn_proj  the 768px attention projection (M = 2560, K = N = 4096) alone
@@ -28,7 +28,7 @@ Prints one JSON line. Besides the required fields it carries:
 Usage: python bench.py [--gpus 1] [--steps K] [--warmup W] [--no-cpu] [--no-extra]
        python bench.py --all-shapes           (every workload shape, one JSON line each)
        python bench.py --recipe               (GELU / SmoothQuant quantizer, shared X)
-       python bench.py --paper-shapes         (the paper's five shapes, tuned vs untuned)
+       python bench.py --paper-shapes         (the paper's five shapes, as shipped and untuned)
        python bench.py --gemm-study           (headline GEMMs on other operand bits, hipBLASLt int8)
        python bench.py --copy-calibration     (a known-size copy for counter scaling)
 """
@@ -348,8 +348,7 @@ class Linear:
                                device=dev)
         self.lws = torch.empty(w8a8.linear_workspace_bytes(M, N, K), dtype=torch.uint8,
                                device=dev)
-        self.tile = w8a8.select_tile(M, N, K)
-        self.tile_name = w8a8.tile_name(self.tile)
+        self.tile_name = w8a8.plan_name(M, N, K)
         self.lib = lib
         P = ctypes.c_void_p
         self.a = {k: P(getattr(self, k).data_ptr())
@@ -648,7 +647,7 @@ def all_shapes(args):
             ops = gemm_ops(M, N, K)
             gb = gemm_bytes(M, N, K)
             rec = {"config": cfg, "shape": shp.name, "M": M, "K": K, "N": N,
-                   "tile": w8a8.tile_name(w8a8.select_tile(M, N, K)),
+                   "tile": w8a8.plan_name(M, N, K),
                    "linear_us": round(lin * 1e3, 2), "gemm_us": round(gem * 1e3, 2),
                    "bf16_linear_us": round(bf * 1e3, 2),
                    "linear_tops": round(ops / lin / 1e9, 1),
@@ -823,11 +822,11 @@ def recipe(args):
 
 def paper_shapes(args):
     """The paper's five model shapes over its token counts (Section 3, "Target
-    architecture"; Section 5 and Table 1): the fused GEMM with the tuned table's tile,
-    with the fallback rule's tile and with one fixed tile (the tuning ablation of
-    Section 3, "Why autotuning is load-bearing"), the whole linear (per-token quantizer
-    + fused GEMM) and bf16 F.linear, on the same synthetic inputs. One JSON line per
-    (shape, M), then one per shape with the ranges over M."""
+    architecture"; Section 5 and Table 1): the fused GEMM as it ships (the default plan),
+    with the tuned table's tile, with the fallback rule's tile and with one fixed tile
+    (the tuning ablation of Section 3, "Why autotuning is load-bearing"), the whole linear
+    (per-token quantizer + fused GEMM) and bf16 F.linear, on the same synthetic inputs.
+    One JSON line per (shape, M), then one per shape with the ranges over M."""
     import torch
     import torch.nn.functional as F
     import paper_2606_14598_amd as w8a8
@@ -848,29 +847,34 @@ def paper_shapes(args):
                              device=dev)
             ops = gemm_ops(M, N, K)
             it = 20 if ops < 5e14 else 5
-            ids = {"tuned": w8a8.select_tile(M, N, K), "default": w8a8.default_tile(M, N, K),
-                   "fixed": FIXED_TILE}
+            ids = {"plan": -1, "tuned": w8a8.select_tile(M, N, K),
+                   "default": w8a8.default_tile(M, N, K), "fixed": FIXED_TILE}
+            gws = torch.empty(max(1, *(w8a8.gemm_workspace_bytes(M, N, K, i)
+                                       for i in ids.values())), dtype=torch.uint8, device=dev)
             t = {}
             for arm, tid in ids.items():
                 same = [a for a in t if ids[a] == tid]
                 t[arm] = t[same[0]] if same else graph_ms(
-                    lambda: w8a8.gemm(xq, sx, wq, sw, bd, tile=tid, out=y), it)
+                    lambda: w8a8.gemm(xq, sx, wq, sw, bd, tile=tid, out=y, workspace=gws), it)
             t["linear"] = graph_ms(lambda: w8a8.linear(xd, wq, sw, bd, out=y, workspace=ws), it)
             t["bf16"] = graph_ms(lambda: F.linear(xd, wd, bd), it)
             rec = {"what": "paper_shape", "shape": name, "M": M, "N": N, "K": K,
-                   "tiles": {a: w8a8.tile_name(i) for a, i in ids.items()},
+                   "tiles": {a: w8a8.plan_name(M, N, K) if i < 0 else w8a8.tile_name(i)
+                             for a, i in ids.items()},
                    "us": {a: round(v * 1e3, 2) for a, v in t.items()},
-                   "tops": {a: round(ops / t[a] / 1e9, 1) for a in ("tuned", "linear", "bf16")},
-                   "gemm_pct_int8_peak": round(100 * ops / t["tuned"] / 1e9 / PEAK_INT8_TOPS, 2),
-                   "speedup_vs_bf16": {"gemm_tuned": round(t["bf16"] / t["tuned"], 3),
+                   "tops": {a: round(ops / t[a] / 1e9, 1) for a in ("plan", "linear", "bf16")},
+                   "gemm_pct_int8_peak": round(100 * ops / t["plan"] / 1e9 / PEAK_INT8_TOPS, 2),
+                   "speedup_vs_bf16": {"gemm": round(t["bf16"] / t["plan"], 3),
+                                       "gemm_tuned": round(t["bf16"] / t["tuned"], 3),
                                        "gemm_default": round(t["bf16"] / t["default"], 3),
                                        "gemm_fixed": round(t["bf16"] / t["fixed"], 3),
                                        "linear": round(t["bf16"] / t["linear"], 3)},
-                   "tuned_over_default": round(t["default"] / t["tuned"], 3),
-                   "tuned_over_fixed": round(t["fixed"] / t["tuned"], 3)}
+                   "plan_over_tuned": round(t["tuned"] / t["plan"], 3),
+                   "plan_over_default": round(t["default"] / t["plan"], 3),
+                   "plan_over_fixed": round(t["fixed"] / t["plan"], 3)}
             print(json.dumps(rec), flush=True)
             recs.append(rec)
-            del xd, wd, bd, wq, sw, xq, sx, y, ws
+            del xd, wd, bd, wq, sw, xq, sx, y, ws, gws
             torch.cuda.empty_cache()
 
         def rng(key, sub):
@@ -878,11 +882,12 @@ def paper_shapes(args):
             return [min(v), max(v)]
         print(json.dumps({"what": "paper_shape_summary", "shape": name, "N": N, "K": K,
                           "M": si.PAPER_M,
-                          "gemm_vs_bf16": rng("speedup_vs_bf16", "gemm_tuned"),
+                          "gemm_vs_bf16": rng("speedup_vs_bf16", "gemm"),
+                          "gemm_tuned_vs_bf16": rng("speedup_vs_bf16", "gemm_tuned"),
                           "gemm_default_vs_bf16": rng("speedup_vs_bf16", "gemm_default"),
                           "gemm_fixed_vs_bf16": rng("speedup_vs_bf16", "gemm_fixed"),
                           "linear_vs_bf16": rng("speedup_vs_bf16", "linear"),
-                          "tuned_tops": rng("tops", "tuned")}), flush=True)
+                          "gemm_tops": rng("tops", "plan")}), flush=True)
 
 
 def gemm_study(args):
@@ -916,7 +921,7 @@ def gemm_study(args):
         }
         ops = gemm_ops(M, N, K)
         rec = {"what": "gemm_study", "shape": name, "M": M, "K": K, "N": N,
-               "tile": w8a8.tile_name(w8a8.select_tile(M, N, K)),
+               "tile": w8a8.plan_name(M, N, K),
                "mean_abs_code": {"x": round(float(xq.float().abs().mean()), 2),
                                  "w": round(float(wq.float().abs().mean()), 2)}}
         us, tops = {}, {}
@@ -968,7 +973,7 @@ def main():
     ap.add_argument("--all-shapes", action="store_true",
                     help="time every workload shape (one JSON line each)")
     ap.add_argument("--paper-shapes", action="store_true",
-                    help="the paper's five model shapes over M = 512..16384, tuned vs untuned")
+                    help="the paper's five model shapes over M = 512..16384, as shipped and untuned")
     ap.add_argument("--gemm-study", action="store_true",
                     help="the headline GEMMs on workload / zero / constant / random codes, "
                          "beside hipBLASLt int8 and bf16")

@@ -147,17 +147,29 @@ w8a8_status w8a8_gemm_acc_i32(const int8_t *xq, const int8_t *wq, int32_t *acc,
  * shape (M within an entry's token range, N and K equal), else the fallback rule's;
  * w8a8_default_tile returns the fallback rule's choice alone, the untuned arm of the
  * tuning ablation. Both return -1 for M <= 0, N <= 0 or K < 0. The _ex variants run a
- * given id for offline sweeps and tests; -1 lets the library choose: the selected id, or
- * for up to 8 tokens a kernel of its own, or above 16 tokens the tile and K split that its
- * cost model prefers. An id outside
- * [0, w8a8_tile_count()) returns W8A8_ERR_ARG. Tiles whose name ends in _k<s> divide K
- * among s workgroups per output tile and sum the int32 partials in a second kernel (the
- * result is the same: integer sums are exact); w8a8_gemm_acc_i32[_ex] runs them
- * unsplit. */
+ * given id for offline sweeps and tests; -1 lets the library choose (w8a8_default_plan).
+ * An id outside [0, w8a8_tile_count()) returns W8A8_ERR_ARG. Tiles whose name ends in
+ * _k<s> divide K among s workgroups per output tile and sum the int32 partials in a
+ * second kernel (the result is the same: integer sums are exact); w8a8_gemm_acc_i32[_ex]
+ * runs them unsplit. */
 int w8a8_tile_count(void);
 const char *w8a8_tile_name(int tile_id);
 int w8a8_select_tile(int64_t M, int64_t N, int64_t K);
 int w8a8_default_tile(int64_t M, int64_t N, int64_t K);
+
+/* What w8a8_gemm runs for a shape with its whole workspace and operands as aligned as K
+ * allows (16 bytes where K % 16 == 0, 4 where K % 4 == 0): the id of an unsplit tile and in
+ * *splits (NULL allowed) the number of K-ranges it is divided into, or
+ *   W8A8_PLAN_ROWS  the kernel for up to 8 tokens that reads whole weight rows;
+ *   W8A8_PLAN_ANY   the kernels for any alignment.
+ * Up to 16 tokens it is the selected tile; above, the tile and K split that the library's
+ * cost model prefers, which need not be the table's. -1 for M <= 0, N <= 0 or K out of
+ * range. w8a8_linear differs where w8a8_linear_one_launch answers 1: there the selected
+ * tile quantizes and multiplies (for one token with K <= 16384 the row kernel). A pure
+ * host query. */
+#define W8A8_PLAN_ROWS (-2)
+#define W8A8_PLAN_ANY (-3)
+int w8a8_default_plan(int64_t M, int64_t N, int64_t K, int *splits);
 
 w8a8_status w8a8_gemm_ex(const int8_t *xq, const float *x_scale, const int8_t *wq,
                          const float *w_scale, const uint16_t *bias, uint16_t *y,

@@ -30,7 +30,8 @@ import torch
 
 __all__ = ["quantize_weight", "quantize_act", "gemm", "linear", "gemm_acc_i32",
            "col_absmax", "smooth_factors", "ACTS",
-           "tile_count", "tile_name", "select_tile", "default_tile", "gemm_workspace_bytes",
+           "tile_count", "tile_name", "select_tile", "default_tile", "default_plan", "plan_name",
+           "gemm_workspace_bytes",
            "linear_workspace_bytes", "linear_one_launch", "library_path", "load_library", "W8A8Error",
            "MAX_K", "version", "mfma_ceiling", "mfma_ceiling_ops", "read_ceiling",
            "READ_BLOCKS"]
@@ -87,6 +88,7 @@ def load_library():
         "w8a8_tile_name": ([INT], ctypes.c_char_p),
         "w8a8_select_tile": ([I64, I64, I64], INT),
         "w8a8_default_tile": ([I64, I64, I64], INT),
+        "w8a8_default_plan": ([I64, I64, I64, ctypes.POINTER(INT)], INT),
         "w8a8_status_string": ([INT], ctypes.c_char_p),
         "w8a8_version": ([], ctypes.c_char_p),
         "w8a8_mfma_ceiling_ops": ([I64], I64),
@@ -184,6 +186,26 @@ def select_tile(M: int, N: int, K: int) -> int:
 def default_tile(M: int, N: int, K: int) -> int:
     """The fallback rule's tile for a shape, ignoring the offline table."""
     return int(load_library().w8a8_default_tile(M, N, K))
+
+
+PLAN_ROWS, PLAN_ANY = -2, -3
+
+
+def default_plan(M: int, N: int, K: int) -> tuple[int, int]:
+    """What gemm() runs for a shape: (unsplit tile id, number of K-ranges), the id PLAN_ROWS
+    for the few-token kernel that reads whole weight rows, PLAN_ANY for the any-alignment
+    kernels. A host query."""
+    splits = ctypes.c_int(1)
+    tile = int(load_library().w8a8_default_plan(M, N, K, ctypes.byref(splits)))
+    return tile, splits.value
+
+
+def plan_name(M: int, N: int, K: int) -> str:
+    """default_plan as text: the tile's name, with _k<s> for s K-ranges."""
+    tile, splits = default_plan(M, N, K)
+    if tile < 0:
+        return {PLAN_ROWS: "rows", PLAN_ANY: "any_alignment"}.get(tile, "none")
+    return tile_name(tile) + (f"_k{splits}" if splits > 1 else "")
 
 
 def _size(name: str, *args) -> int:

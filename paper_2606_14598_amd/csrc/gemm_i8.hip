@@ -2208,6 +2208,19 @@ GemmPlan select_plan(int64_t M, int64_t N, int64_t K) {
     return p;
 }
 
+int default_plan(int64_t M, int64_t N, int64_t K, int *splits) {
+    const GemmPlan p = select_plan(M, N, K);
+    const TileInfo &t = kTiles[p.tile].info;
+    *splits = 1;
+    if (any_alignment_only(M, K) || (K % 16 != 0 && !t.dword))
+        return kPlanAny;
+    if (gemv_shape(M, N, K, false))
+        return kPlanRows;
+    if (p.splits > 1)
+        *splits = split_count(t, p.splits, K, nullptr);
+    return t.base >= 0 ? t.base : p.tile;
+}
+
 // LDS of one workgroup on gfx950.
 constexpr int64_t kLdsPerWorkgroup = 160 * 1024;
 

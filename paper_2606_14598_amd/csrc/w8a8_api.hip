@@ -22,6 +22,7 @@ w8a8_status from_hip(hipError_t e) { return e == hipSuccess ? W8A8_OK : W8A8_ERR
 
 bool aligned16(const void *p) { return reinterpret_cast<uintptr_t>(p) % 16 == 0; }
 
+static_assert(W8A8_PLAN_ROWS == kPlanRows && W8A8_PLAN_ANY == kPlanAny, "plan ids");
 static_assert(W8A8_ACT_NONE == ACT_NONE && W8A8_ACT_GELU == ACT_GELU, "act codes");
 
 bool act_ok(int act) { return act == W8A8_ACT_NONE || act == W8A8_ACT_GELU; }
@@ -369,6 +370,15 @@ int w8a8_default_tile(int64_t M, int64_t N, int64_t K) {
     if (M <= 0 || N <= 0 || K < 0)
         return -1;
     return default_tile(M, N, K);
+}
+
+int w8a8_default_plan(int64_t M, int64_t N, int64_t K, int *splits) {
+    int n = 1;
+    const bool ok = M > 0 && N > 0 && K >= 0 && K <= W8A8_MAX_K && product_ok(M, N);
+    const int id = ok ? default_plan(M, N, K, &n) : -1;
+    if (splits)
+        *splits = n;
+    return id;
 }
 
 const char *w8a8_status_string(w8a8_status status) {

@@ -65,6 +65,10 @@ int default_tile(int64_t M, int64_t N, int64_t K);
 // selected tile, or a tile with K split where that leaves fewer CUs idle.
 GemmPlan tile_plan(int id);
 GemmPlan select_plan(int64_t M, int64_t N, int64_t K);
+// What launch_gemm runs for that plan on operands as aligned as K allows: the unsplit tile
+// and its K-ranges, or one of the two below (*splits is 1 then).
+constexpr int kPlanRows = -2, kPlanAny = -3;
+int default_plan(int64_t M, int64_t N, int64_t K, int *splits);
 // Extra device scratch a plan needs for a shape: the int32 partial products of a split
 // one (splits x M x N x 4 bytes), 0 for the others.
 size_t plan_workspace_bytes(const GemmPlan &p, int64_t M, int64_t N, int64_t K);

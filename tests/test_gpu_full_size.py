@@ -7,8 +7,10 @@ times:
     768px MLP, the four 1024px linears, the skinny and odd shapes);
   * the paper's five model shapes at its in-model token count M = 4110 (Section 5, "The
     kernel is exact and the GEMMs are compute-bound": bit-exact on all five shapes),
-    and one token bucket for every other tile the table selects for them (the
-    96-channel tiles, the split-K tiles at K = 53248, the 256-row tiles);
+    and one token bucket for every other tile that runs them (the 96-channel tiles, the
+    K splits at K = 53248, the 256-row tiles);
+  * the table's tile that the default plan overrides above 8 tokens (llm_proj at 512),
+    forced through w8a8_gemm_ex;
   * the two table tiles that serve only M >= 12289 run, forced through w8a8_gemm_ex,
     at a smaller M with their shapes' own N and K.
 Bars: codes, scale bits and the accumulator exact; bf16 within 1 ulp with cosine >=
@@ -40,9 +42,8 @@ def _full_compare(shp, tile=None):
     w8a8_gemm_ex with a forced tile) and the oracle's chain on the CPU, and compare every
     element."""
     M, K, N = shp.M, shp.K, shp.N
-    chosen = w8a8.select_tile(M, N, K) if tile is None else tile
-    say(f"full {shp.name}: M={M} K={K} N={N} dist={shp.dist} seed={shp.seed} "
-        f"tile={w8a8.tile_name(chosen)}{' (forced)' if tile is not None else ''}")
+    ran = w8a8.plan_name(M, N, K) if tile is None else f"{w8a8.tile_name(tile)} (forced)"
+    say(f"full {shp.name}: M={M} K={K} N={N} dist={shp.dist} seed={shp.seed} tile={ran}")
     x, w, b = si.make_inputs(shp)
     wq_o, sw_o = oracle.quantize_rows(w)
     wq, sw = w8a8.quantize_weight(dev_bf16(w))
@@ -55,7 +56,10 @@ def _full_compare(shp, tile=None):
         y = host_bits(w8a8.linear(xd, wq, sw, bd))
     else:
         y = host_bits(w8a8.gemm(xq, sx, wq, sw, bd, tile=tile))
-    acc = host(w8a8.gemm_acc_i32(xq, wq))
+    # The accumulator of the tile that produced y (unsplit: the debug path has no split),
+    # where that is a tile.
+    same = w8a8.default_plan(M, N, K)[0] if tile is None else tile
+    acc = host(w8a8.gemm_acc_i32(xq, wq, tile=max(same, -1)))
     xq_h, sx_h = host(xq), host(sx)
     del xd, xq, wq
     torch.cuda.empty_cache()
@@ -76,9 +80,9 @@ def test_workload_full_tensors(config, name):
     _full_compare(si.workload(config, name))
 
 
-# The paper's shapes at M = 4110, then a bucket for each other tile the table selects:
-# 96-channel tiles (attn_out / ffn_down at 512 and 1024 tokens), split-K tiles (llm_proj
-# at 512 and 1024, K = 53248), 256 x 128 (qkv at 512), 256 x 256 eight-wavefront (qkv at
+# The paper's shapes at M = 4110, then a bucket for each other tile that runs them:
+# 96-channel tiles (attn_out / ffn_down at 512 and 1024 tokens), K splits (llm_proj at 512
+# seven ways and at 1024 two ways, K = 53248), 256 x 128 (qkv at 512), 256 x 256 eight-wavefront (qkv at
 # 1024).
 PAPER_CASES = [(p[0], 4110) for p in si.PAPER_SHAPES] + [
     ("attn_out", 512), ("attn_out", 1024), ("ffn_down", 512), ("ffn_down", 1024),
@@ -88,6 +92,14 @@ PAPER_CASES = [(p[0], 4110) for p in si.PAPER_SHAPES] + [
 @pytest.mark.parametrize("name,M", PAPER_CASES)
 def test_paper_shape_full_tensors(name, M):
     _full_compare(si.paper_shape(name, M))
+
+
+def test_overridden_table_tile_full_tensors():
+    shp = si.paper_shape("llm_proj", 512)
+    table = w8a8.select_tile(shp.M, shp.N, shp.K)
+    assert w8a8.tile_name(table) == "m256n128k128w2x2s3_k2"
+    assert w8a8.plan_name(shp.M, shp.N, shp.K) == "m256n256k64w2x4s4_k7"
+    _full_compare(shp, tile=table)
 
 
 # Tiles the table picks only for M >= 12289 (ffn_down: m256n256k128w2x2s2, llm_proj:

@@ -554,7 +554,7 @@ def test_random_shapes_against_oracle(M, K, N):
     """w8a8_linear on the default tile of each shape against the oracle's linear: codes
     and scales exact, the int32 accumulator exact through the debug path, the bf16
     output within the bf16 gate."""
-    say(f"random shape M={M} K={K} N={N} tile={w8a8.tile_name(w8a8.select_tile(M, N, K))}")
+    say(f"random shape M={M} K={K} N={N} tile={w8a8.plan_name(M, N, K)}")
     x, w, b = si.make_inputs((M, K, N), seed=M * 31 + K * 7 + N, dist="student_t")
     wq_o, sw_o = oracle.quantize_rows(w)
     y_o, xq_o, sx_o, acc_o = oracle.linear(x, wq_o, sw_o, b)
@@ -576,7 +576,7 @@ EXTREME_SHAPES = [(1, 4096, 40000), (65536, 64, 40), (3, 133136, 8), (2, 133136,
 def test_extreme_aspect_shapes_against_oracle(M, K, N):
     """A wide weight at one token (2500 workgroups), many tokens on a tiny weight, K near
     its maximum on tiny M and N: every output against the oracle's linear."""
-    say(f"extreme shape M={M} K={K} N={N} tile={w8a8.tile_name(w8a8.select_tile(M, N, K))}")
+    say(f"extreme shape M={M} K={K} N={N} tile={w8a8.plan_name(M, N, K)}")
     x, w, b = si.make_inputs((M, K, N), seed=M + 3 * K + 7 * N, dist="outlier")
     wq_o, sw_o = oracle.quantize_rows(w)
     y_o, xq_o, sx_o, acc_o = oracle.linear(x, wq_o, sw_o, b)

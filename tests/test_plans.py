@@ -26,6 +26,33 @@ def test_any_alignment_sizes_need_no_partials(M, N, K):
     assert lib.w8a8_linear_workspace_least_bytes(M, N, K) == head
 
 
+def test_default_plan_says_what_runs():
+    """The query agrees with the workspace that the same plan asks for, names the kernels
+    that are no tiles, and rejects what the GEMM rejects."""
+    seen = set()
+    for M in (1, 2, 8, 16, 17, 33, 64, 128, 129, 333, 512, 640, 2560, 4608):
+        for N in (128, 1000, 4096, 4608, 16384):
+            for K in (256, 1000, 1004, 1001, 4096, 8200, 16384, 53248):
+                tile, splits = w8a8.default_plan(M, N, K)
+                seen.add(min(tile, 0))
+                partials = splits * M * N * 4 if splits > 1 else 0
+                assert w8a8.gemm_workspace_bytes(M, N, K) == partials, (M, N, K)
+                any_only = K % 4 != 0 or (K % 16 != 0 and M <= 32)
+                if any_only:
+                    assert tile == w8a8.PLAN_ANY, (M, N, K)
+                if tile == w8a8.PLAN_ROWS:
+                    assert M <= 8 and K % 16 == 0
+                if tile >= 0:
+                    name = w8a8.tile_name(tile)
+                    assert not re.search(r"_k\d+$", name)
+                    assert w8a8.plan_name(M, N, K) == name + (f"_k{splits}" if splits > 1 else "")
+    assert seen == {0, w8a8.PLAN_ROWS, w8a8.PLAN_ANY}
+    assert w8a8.plan_name(512, 4608, 53248) == "m256n256k64w2x4s4_k7"
+    assert w8a8.plan_name(1, 4096, 4096) == "rows"
+    for bad in ((0, 8, 8), (8, 0, 8), (8, 8, -1), (8, 8, w8a8.MAX_K + 1)):
+        assert w8a8.default_plan(*bad) == (-1, 1)
+
+
 def test_sizes_beside_them_keep_their_partials():
     assert w8a8.gemm_workspace_bytes(64, 4096, 8192) > 0
     assert w8a8.gemm_workspace_bytes(33, 640, 24572) > 0
