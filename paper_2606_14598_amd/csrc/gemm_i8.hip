@@ -1484,7 +1484,7 @@ __global__ void __launch_bounds__(256) gemv_i8_kernel(KParams kp) {
     const int rows = n0 >= N ? 0 : (int)(N - n0 < R ? N - n0 : R);
     const int64_t nb = rows > 0 ? n0 : 0;      // a wavefront past N reads and stores nothing
     const int turns = (K + CH - 1) / CH, padded = turns * CH;
-    // Codes, token rows of `padded` bytes with zeros from K on; behind them 4 row maxima.
+    // Codes, token rows of `padded` bytes with zeros from K on; with QX 4 row maxima behind them.
     extern __shared__ __attribute__((aligned(1024))) int8_t gemv_lds[];
     int8_t *const xs = gemv_lds;
     uint32_t *const pmax = reinterpret_cast<uint32_t *>(gemv_lds + MT * padded);
@@ -1785,7 +1785,7 @@ bool gemv_shape(int64_t M, int64_t N, int64_t K, bool quantize) {
 template <int J>
 void launch_gemv_j(const KParams &kp, hipStream_t s) {
     const dim3 grid((unsigned)((kp.a.N + 32 / J - 1) / (32 / J))), block(256);
-    const size_t lds = (size_t)gemv_code_bytes(kp.a.M, kp.a.K) + 16;
+    const size_t lds = (size_t)gemv_code_bytes(kp.a.M, kp.a.K) + (kp.x ? 16 : 0);   // QX: maxima
     if (kp.x && kp.a.K <= 8192)
         hipLaunchKernelGGL((gemv_i8_kernel<J, 1, true>), grid, block, lds, s, kp);
     else if (kp.x)
