@@ -1762,10 +1762,12 @@ struct WsxTile {
 // workgroups per CU (32 KB); the token it quantizes itself has at most 16384 values (eight
 // 16-byte loads a thread). Against the streaming tiles' GEMM, over 30 shapes each: 1.2-2.9x
 // for one token, 1.1-2.6x for two, 1.05-2.0x for up to four. With more tokens the sums'
-// reduction shows, and only weights of 32 MB and more gain (7 tokens: 18432 x 3072 20.0 -> 16.0
-// us, 16384 x 4096 18.0 -> 16.2; but 5072 x 480 4.7 -> 5.3).
+// reduction shows, and only weights of 32 MB and more on 16384 channels and more gain
+// (weights from HBM, 8 tokens: 16384 x 4096 17.4 -> 15.9 us, 18432 x 2048 14.6 -> 11.2;
+// but 12288 x 4096 13.2 -> 13.8, 12288 x 3072 10.9 -> 11.5: below 16384 channels the
+// token-block-in-LDS tile runs).
 constexpr int64_t kGemvLds = 32 << 10;
-constexpr int64_t kGemvManyTokens = 32 << 20;
+constexpr int64_t kGemvManyTokens = 32 << 20, kGemvManyChannels = 16384;
 
 int gemv_j(int64_t K) { return K <= 2048 ? 2 : K <= 4096 ? 4 : 8; }
 
@@ -1777,7 +1779,7 @@ int64_t gemv_code_bytes(int64_t M, int64_t K) {
 bool gemv_shape(int64_t M, int64_t N, int64_t K, bool quantize) {
     if (M < 1 || M > (quantize ? 1 : 8) || K < 16 || K % 16 != 0 || N > (int64_t)1 << 31)
         return false;
-    if (M > 4 && N * K < kGemvManyTokens)
+    if (M > 4 && (N < kGemvManyChannels || N * K < kGemvManyTokens))
         return false;
     return quantize ? K <= 16384 : gemv_code_bytes(M, K) <= kGemvLds;
 }

@@ -53,6 +53,17 @@ def test_default_plan_says_what_runs():
         assert w8a8.default_plan(*bad) == (-1, 1)
 
 
+@pytest.mark.parametrize("M", [5, 8])
+def test_row_kernel_at_five_to_eight_tokens(M):
+    """Only where it beats the tile that ran before it: on 16384 channels and more with a
+    weight of 32 MB."""
+    for N, K in ((16384, 2048), (16384, 4096), (20480, 2048)):
+        assert w8a8.plan_name(M, N, K) == "rows", (N, K)
+    for N, K in ((12288, 4096), (16383, 4096), (12288, 3072), (16384, 2032), (20480, 1024)):
+        assert w8a8.plan_name(M, N, K) != "rows", (N, K)
+    assert w8a8.plan_name(4, 12288, 4096) == "rows"
+
+
 def test_sizes_beside_them_keep_their_partials():
     assert w8a8.gemm_workspace_bytes(64, 4096, 8192) > 0
     assert w8a8.gemm_workspace_bytes(33, 640, 24572) > 0
