@@ -104,6 +104,36 @@ def test_k_is_split_only_where_the_best_unsplit_tile_takes_over_12_us():
     assert split > 50
 
 
+def test_fit_recovers_the_costs_of_a_synthetic_sweep():
+    from paper_2606_14598_amd import tune
+    names = [w8a8.tile_name(i) for i in range(w8a8.tile_count())]
+    rng = np.random.default_rng(7)
+    stream = [n for n in names if n.startswith(("skinny", "wsx"))]
+    tiles = [n for n in names if n not in tune.UNMODELED and n not in stream
+             and not re.search(r"_k\d+$", n)]
+    want = {n: rng.uniform(0.5, 2, 8) * [3, 1, 1, 1, .05, .05, .05, .2] for n in stream}
+    want |= {n: rng.uniform(0.5, 2, 2) * [5e-3, 0.2] for n in tiles}
+    import random
+    r, rows = random.Random(1), []
+    for i in range(400):
+        M, N, K = tune.random_shape(r, 128 if i % 2 else 8192)
+        assert 17 <= M <= 8192 and K % 16 == 0 and N % 16 == 0
+        us = {n: float(np.dot(want[n], tune.cost_terms(n, M, N, K))) for n in tiles}
+        if M <= 128:
+            # a token block that does not fit runs another kernel: it must not be fitted
+            us |= {n: float(np.dot(want[n], tune.cost_terms(n, M, N, K)))
+                   * (1 if tune.stream_fits(n, M, K) else 3) for n in stream}
+        rows.append({"M": M, "N": N, "K": K, "us": us})
+    got = tune.fit_costs(rows, names)
+    assert set(got) == set(want)
+    for n in want:
+        for row in rows[::7]:
+            M, N, K = row["M"], row["N"], row["K"]
+            if n in row["us"] and (n in tiles or tune.stream_fits(n, M, K)):
+                t = float(np.dot(got[n], tune.cost_terms(n, M, N, K)))
+                assert abs(t / row["us"][n] - 1) < 1e-6, n
+
+
 @pytest.mark.gpu
 @pytest.mark.parametrize("M,N,K", [(64, 1000, 8193), (20, 4096, 8200)])
 def test_any_alignment_gemm_without_a_workspace(M, N, K):
