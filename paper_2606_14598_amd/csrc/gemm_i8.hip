@@ -1966,9 +1966,21 @@ struct TileCost {
     double c;   // ms per round, fixed part
     double d;   // ms per round per 1e9 (K * TM * TN)
 };
+// A weight-streaming tile, in us: fixed part and per 1000 of K for the first round of 256
+// workgroups, the same for each further one, per MB of weight rows and of token rows that
+// the workgroups read, per MB of weights, and per 1000 of K more where rows start at a
+// multiple of 256 bytes (the 16 rows of a fragment then fall on the same few memory
+// channels: 5-20% longer).
+struct StreamCost {
+    int tile;
+    double fixed, k, round, round_k, w, x, weights, k256;
+};
 #include "tile_table.inc"
 
 static_assert(sizeof(kTileCost) / sizeof(kTileCost[0]) == kNumTiles, "one cost per tile");
+
+// LDS of one workgroup on gfx950.
+constexpr int64_t kLdsPerWorkgroup = 160 * 1024;
 
 // Cost of a split besides its main launch, in us: a second launch, its reads of each
 // partial, and one write and one read of the partials' bytes.
@@ -1981,25 +1993,6 @@ constexpr int64_t kSplitWorkspace = 80 << 20;   // bytes of partials at most
 constexpr double kSplitWorthUs = 12.0;
 // A table entry, which was timed on its own shape, gives way only to a clear gain.
 constexpr double kOverTable = 0.85;
-
-// The weight-streaming tiles, in us: fixed part, per 1000 of K, per round of 256 workgroups,
-// and per MB of weight rows and of token rows that the workgroups read. Fitted like
-// kTileCost, on the shapes of up to 128 tokens.
-struct StreamCost {
-    int tile;
-    double fixed, k, round, w, x;
-};
-const StreamCost kStreamCost[] = {
-    {15, 3.168, 0.419, 0.602, 0.1546, 0.0000},  // skinny_m16n16w16
-    {16, 3.064, 0.732, 0.671, 0.1872, 0.0148},  // skinny_m32n16w16
-    {17, 1.979, 1.478, 2.020, 0.0019, 0.5314},  // skinny_m16n64w16
-    {18, 1.511, 1.437, 2.594, 0.1029, 0.0544},  // skinny_m64n32w16
-    {19, 0.317, 2.092, 4.337, 0.0757, 0.1143},  // skinny_m128n32w8
-    {36, 3.808, 0.355, 0.603, 0.0001, 0.1572},  // wsx_m16n16w8d4
-    {37, 3.208, 0.723, 1.585, 0.0000, 0.2670},  // wsx_m16n32w8d4
-    {38, 2.324, 1.419, 3.660, 0.0000, 0.5010},  // wsx_m16n64w8d4
-    {39, 3.388, 0.983, 0.916, 0.1310, 0.0304},  // wsx_m32n32w8d2
-};
 
 // Shapes without a table entry, no split. Above 128 tokens a wave-quantization cost model
 // picks the tile: a launch of T workgroups on 256 CUs takes ceil(T / 256) rounds, and a
@@ -2119,19 +2112,34 @@ static double stream_cost_us(const StreamCost &c, int64_t M, int64_t N, int64_t 
     const TileInfo &t = kTiles[c.tile].info;
     const int64_t wgs = ((M + t.tm - 1) / t.tm) * ((N + t.tn - 1) / t.tn);
     const int64_t rows = M < t.tm ? M : t.tm;
-    return c.fixed + c.k * 1e-3 * (double)K + c.round * (double)((wgs + 255) / 256) +
-           1e-6 * (double)(wgs * K) * (c.w * t.tn + c.x * (double)rows);
+    return c.fixed + c.k * 1e-3 * (double)K +
+           (c.round + c.round_k * 1e-3 * (double)K) * (double)((wgs - 1) / 256) +
+           1e-6 * ((double)(wgs * K) * (c.w * t.tn + c.x * (double)rows) +
+                   c.weights * (double)(N * K)) +
+           (K % 256 == 0 ? c.k256 * 1e-3 * (double)K : 0.0);
+}
+
+// Whether a streaming tile runs its own kernel: the token block of the tiles that keep it in
+// LDS has to fit there (WsxTile::launch).
+static bool stream_fits(const TileInfo &t, int64_t M, int64_t K) {
+    return t.streaming != 2 ||
+           wsx_lds_bytes(M < t.tm ? M : t.tm, K, false, t.tm / 16, t.tn / 16, t.threads / 64) <=
+               kLdsPerWorkgroup;
 }
 
 // What runs a shape by default. Up to 16 tokens, and where K sends the operands to the
 // any-alignment kernels, the selected tile. Above, the least predicted time over the tiles,
 // each unsplit and with K split in as many ways as fit one round of workgroups; a table
-// entry stays unless the prediction beats its own clearly. On 1100 random shapes (M
-// 17..8192, N 128..20480, K 256..24576) the choice is within 1.8% of the fastest plan above
-// 128 tokens (geometric mean; 5% below 32, 3.4% up to 64, 1.5% up to 128), where the table's
-// fallback was 22% off (12, 16 and 28%): long K on few output tiles left most CUs idle
-// (512 x 4608 x 53248: 162.7 us split in two, 138.8 in seven on 252 workgroups), and tiles
-// without a deep ring were taken for small outputs (640 x 1024 x 4096: 20.7 against 11.0 us).
+// entry stays unless the prediction beats its own clearly. On 900 random shapes (tune.py
+// --random, other ones than the costs were fitted to; weights from HBM) the choice is within
+// 0.6% of the fastest tile for 17 to 32 tokens (geometric mean), 0.8% up to 64, 1.2% up to
+// 128 and 2.0% above; the fallback tile 16, 19, 31 and 10%: long K on few output tiles left
+// most CUs idle (512 x 4608 x 53248: 162.7 us split in two, 138.8 in seven on 252
+// workgroups), and tiles without a deep ring were taken for small outputs (640 x 1024 x
+// 4096: 20.7 against 11.0 us). The streaming tiles' costs hold for the kernels of their
+// own: fitted over all K they described the token-block-in-LDS tiles together with the
+// kernel that replaces them where the block does not fit, and 33 to 64 tokens went to other
+// tiles (64 x 4096 x 4096 11.4 us, 9.8 now; 40 x 3072 x 3072 10.6, 7.4).
 static GemmPlan compute_plan(int64_t M, int64_t N, int64_t K) {
     const int table = table_tile(M, N, K);
     GemmPlan best = tile_plan(table >= 0 ? table : fallback_tile(M, N, K));
@@ -2163,7 +2171,8 @@ static GemmPlan compute_plan(int64_t M, int64_t N, int64_t K) {
     };
     if (M <= 128 && aligned)
         for (const StreamCost &c : kStreamCost)
-            consider(c.tile, 1, stream_cost_us(c, M, N, K));
+            if (stream_fits(kTiles[c.tile].info, M, K))
+                consider(c.tile, 1, stream_cost_us(c, M, N, K));
     const uint32_t by_space = (uint32_t)(kSplitWorkspace / 4 / (mn > 1.0 ? mn : 1.0));
     for (int id = 0; id < kNumTiles; ++id) {
         const TileInfo &t = kTiles[id].info;
@@ -2222,9 +2231,6 @@ int default_plan(int64_t M, int64_t N, int64_t K, int *splits) {
         *splits = split_count(t, p.splits, K, nullptr);
     return t.base >= 0 ? t.base : p.tile;
 }
-
-// LDS of one workgroup on gfx950.
-constexpr int64_t kLdsPerWorkgroup = 160 * 1024;
 
 // The small fused linear (see gemm_i8_skinny_kernel, QX): the chosen tile streams the
 // weight, K % 16 == 0 with 16-byte aligned operands, a token block's codes and scales fit

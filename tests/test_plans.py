@@ -104,6 +104,39 @@ def test_k_is_split_only_where_the_best_unsplit_tile_takes_over_12_us():
     assert split > 50
 
 
+def test_cost_rows_stand_at_their_tiles():
+    """The costs are matched to the tiles by position (kTileCost) or id (kStreamCost): the
+    tile that a row was fitted for is the one named beside it."""
+    path = os.path.join(os.path.dirname(w8a8.__file__), "csrc", "tile_table.inc")
+    text = open(path).read()
+    rows = text[text.index("kTileCost[] = {"):text.index("kStreamCost[] = {")]
+    names = re.findall(r"\},  // (\w+)", rows)
+    assert names == [w8a8.tile_name(i) for i in range(w8a8.tile_count())]
+    rows = text[text.index("kStreamCost[] = {"):text.index("kTileTable[]")]
+    ids = re.findall(r"\{(\d+), [^}]*\},  // (\w+)", rows)
+    assert [w8a8.tile_name(int(i)) for i, _ in ids] == [name for _, name in ids]
+    assert {n for _, n in ids} == {n for n in names if n.startswith(("skinny", "wsx"))}
+
+
+def test_token_block_tiles_only_where_the_block_fits_in_lds():
+    """Above 16 tokens the plan takes a tile that keeps its token block in LDS only where it
+    does (elsewhere that id runs another kernel, which the tile's cost does not describe),
+    and does take it where it was measured fastest (33 to 64 tokens)."""
+    from paper_2606_14598_amd.tune import stream_fits
+    for M, N, K in ((64, 4096, 4096), (40, 3072, 3072), (33, 3072, 3072), (56, 4096, 4096)):
+        assert w8a8.plan_name(M, N, K) == "wsx_m32n32w8d2", (M, N, K)
+    rng = np.random.default_rng(3)
+    seen = 0
+    for _ in range(3000):
+        M, N = int(rng.integers(17, 129)), int(2 ** rng.uniform(7, 14))
+        K = int(2 ** rng.uniform(8, 14.6)) // 16 * 16
+        name = w8a8.plan_name(M, N, K)
+        if name.startswith("wsx"):
+            seen += 1
+            assert stream_fits(name, M, K), (M, N, K, name)
+    assert seen > 300
+
+
 def test_fit_recovers_the_costs_of_a_synthetic_sweep():
     from paper_2606_14598_amd import tune
     names = [w8a8.tile_name(i) for i in range(w8a8.tile_count())]
