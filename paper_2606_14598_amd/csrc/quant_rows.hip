@@ -864,14 +864,27 @@ hipError_t launch_col_absmax(const uint16_t *v, int64_t rows, int64_t K, int act
         while (lpr_log2 < 6 && (1 << lpr_log2) < nvec)
             ++lpr_log2;
         const int64_t kb = (nvec + (1 << lpr_log2) - 1) >> lpr_log2;
-        // Rows of one full batch per thread. Blocks of 1024 threads, two per CU (the chip's
-        // resident threads), so that few atomics meet on a column (16384 x 4096: 34.4 us,
-        // 50.8 on 2048 blocks of 256); 256 threads where that leaves few row blocks and the
-        // loads' latency counts (300 x 1000: 5.6 against 6.9 us), unless one block of 1024
-        // holds all rows and needs no zeroing before it (64 x 4096: 3.8 against 5.7 us).
-        const int64_t batch256 = 8 * (256 >> lpr_log2);
-        const int threads = rows <= 4 * batch256 || rows > 16 * batch256 ? kColThreads : 256;
-        const int64_t unit = batch256 * (threads / 256);
+        // Eight rows in flight per thread (figures: matrices in turn from 300 MB). One block for
+        // all rows where it can hold them: it
+        // needs no zeroing before it (128 x 4096: 5.0 us, 6.1 on blocks of 512). It takes as
+        // few threads as leave four rows for each, since the merge walks a column's row
+        // groups one by one: at least 16 groups or 512 threads (1 x 4096 with GELU: 3.8 us,
+        // 4.5 on 1024; 1 x 64 with GELU: 3.7 on 128, 10.2 on 1024), at most 64 groups. Beyond, blocks
+        // of 1024 threads, two per CU (the chip's resident threads), so that few atomics
+        // meet on a column (16384 x 4096: 32.0 us, 36.9 on 256); 256 threads where that
+        // leaves few row blocks and the loads' latency counts (300 x 1000: 6.2 against 7.2
+        // us), 512 between, up to 48 blocks of 1024 (1000 x 1001: 7.4 us, 8.5 on 1024, 7.6 on
+        // 256), all with at most 16 row groups (16384 x 64: 7.9 us on 128, 9.7 on 1024).
+        const int64_t batch = 8 * (kColThreads >> lpr_log2);
+        const int merge16 = 16 << lpr_log2, merge64 = 64 << lpr_log2;
+        int threads = merge16 < 64 ? 64 : merge16 < 512 ? merge16 : 512;
+        while (threads < kColThreads && threads < merge64 && 4 * (threads >> lpr_log2) < rows)
+            threads *= 2;
+        if (8 * (threads >> lpr_log2) < rows) {
+            threads = rows <= 4 * batch ? 256 : kb * rows <= 48 * batch ? 512 : kColThreads;
+            threads = threads < merge16 ? threads : merge16 < 64 ? 64 : merge16;
+        }
+        const int64_t unit = 8 * (threads >> lpr_log2);
         const int64_t want = kb < 512 ? 512 / kb : 1;
         int64_t rpb = ((rows + want - 1) / want + unit - 1) / unit * unit;
         while ((rows + rpb - 1) / rpb > 65535)

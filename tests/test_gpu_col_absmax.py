@@ -57,3 +57,18 @@ def test_col_absmax_special_values():
     g = w8a8.col_absmax(x, act="gelu").cpu()
     # GELU(-inf) is -inf * 0
     assert math.isnan(g[1]) and math.isnan(g[2]) and g[4] == inf and g[5] == 0.0
+
+
+@pytest.mark.parametrize("K", [3, 8, 64, 70, 256, 520, 1001, 4096])
+def test_col_absmax_block_sizes(K):
+    """Row counts at the edges of the launch rule: one block of 64 to 1024 threads, several
+    of 64 to 1024, and the last partial one."""
+    lanes = min(64, 1 << (-(-K // 8) - 1).bit_length())
+    one = {8 * max(1, t // lanes) for t in (64, 128, 256, 512, 1024)}
+    for rows in sorted({1, *one, *(r + 1 for r in one), 4 * max(one), 4 * max(one) + 1}):
+        x, _, _ = si.make_inputs((rows, K, 1), seed=rows + K, dist="preact")
+        assert np.array_equal(w8a8.col_absmax(_dev(x)).cpu().numpy(), oracle.col_absmax(x)), rows
+        if rows <= 600:
+            g = w8a8.col_absmax(_dev(x), act="gelu").cpu().numpy()
+            want = oracle.col_absmax(x, act="gelu")
+            assert np.all(np.abs(g - want) <= 2.0 ** -17 * want), rows
