@@ -647,6 +647,11 @@ hipError_t launch_rows(const uint16_t *v, int64_t rows, int64_t K, const float *
         // would not fit 128 VGPRs): a 1024-thread block per row, still read once. The
         // looped kernel below reads such rows twice, the second time mostly from the
         // MALL, since 32 CUs' rows overflow an XCD's L2.
+        // Up to K = 24576 three vectors a thread, so that few lanes work on nothing
+        // (4608 x 16400 with the multiplier: 47.8 us, 50.6 on four; 7-13% over K = 16400,
+        // 18432, 20480 and 24576, 1 to 4608 rows and every transform).
+        if (nvec <= 3072)
+            return launch_reg<1024, 3, ACT, CM>(v, rows, K, colmul, q, scale, s);
         if (nvec <= 4096)
             return launch_reg<1024, 4, ACT, CM>(v, rows, K, colmul, q, scale, s);
         if constexpr (PLAIN)

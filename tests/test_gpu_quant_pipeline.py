@@ -42,6 +42,23 @@ def test_gelu_rows_beyond_the_grid(rows, K):
     check_gelu_codes(x, host(q), host(s), q_o, s_o, None, f"{rows}x{K}")
 
 
+@pytest.mark.parametrize("rows,K", [(3, 16392), (1030, 20488), (515, 24576), (3, 24584)])
+def test_three_vectors_a_thread(rows, K):
+    """The edges of the 1024 x 3 mapping, with every transform."""
+    say(f"quantizer 1024 x 3 rows={rows} K={K}")
+    x, _, _ = si.make_inputs((rows, K, 1), seed=rows + K, dist="preact")
+    cm = np.random.default_rng(K).uniform(0.05, 8, K).astype(np.float32)
+    for act in ("none", "gelu"):
+        for c in (None, cm):
+            q_o, s_o = oracle.quantize_rows(x, act=act, col_mul=c)
+            q, s = w8a8.quantize_act(dev_bf16(x), act=act,
+                                     col_mul=None if c is None else dev_f32(c))
+            if act == "none":
+                assert np.array_equal(host(q), q_o) and np.array_equal(host(s), s_o)
+            else:
+                check_gelu_codes(x, host(q), host(s), q_o, s_o, c, f"{rows}x{K}")
+
+
 def test_output_rows_at_eight_bytes():
     """Codes into rows at an 8-byte offset: no 16-byte streaming stores."""
     lib = w8a8.load_library()
