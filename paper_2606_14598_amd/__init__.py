@@ -114,13 +114,20 @@ def _call(name: str, *args) -> None:
         raise W8A8Error(name, st, load_library().w8a8_status_string(st).decode())
 
 
+# What torch.cuda.current_device and current_stream ask, without their wrappers' host time;
+# the public calls where a torch build does not have them under these names.
+_current_device = getattr(torch._C, "_cuda_getDevice", torch.cuda.current_device)
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream",
+                      lambda index: torch.cuda.current_stream(index).cuda_stream)
+
+
 def _launch(device: torch.device, name: str, *args) -> None:
     """_call with `device` current and its current stream as the last argument. The device
     is switched only where it is another one: a call's host time is what a small linear
     costs."""
     index = device.index
-    if index is not None and torch._C._cuda_getDevice() == index:
-        _call(name, *args, torch._C._cuda_getCurrentRawStream(index))
+    if index is not None and _current_device() == index:
+        _call(name, *args, _raw_stream(index))
     else:
         with torch.cuda.device(device):
             _call(name, *args, torch.cuda.current_stream(device).cuda_stream)
