@@ -26,16 +26,20 @@
  *   - Tensor pointers are device pointers (HIP device memory of the current device);
  *     `stream` is a hipStream_t (NULL = the legacy default stream). All work is
  *     enqueued on `stream`; no call synchronizes, allocates or frees memory.
- *   - The caller owns every buffer. The library keeps no state besides its immutable
- *     kernel and tile tables, so concurrent calls on different streams are safe when
- *     their output and workspace buffers do not overlap.
+ *   - The caller owns every buffer. Besides its immutable kernel and tile tables the
+ *     library keeps, for each thread, the plans it chose for the last sizes (a pure
+ *     function of M, N and K), and the scratch of w8a8_linear_noalloc. Concurrent calls
+ *     on different streams or from different threads are safe when their output and
+ *     workspace buffers do not overlap.
  *   - Arguments are validated before anything is launched; on a non-zero status
  *     nothing was enqueued (W8A8_ERR_HIP excepted: a launch that HIP rejected).
  *   - M == 0 or N == 0 is a valid no-op. K == 0 is valid: every code is 0, every
  *     scale 0, and Y = b.
  *   - Inputs must be finite; for non-finite X, W or b the results are unspecified.
- *   - Any alignment and any K are accepted; 16-byte aligned operands with K a multiple
- *     of 16 take the fast kernels, others a slower generic kernel with the same results.
+ *   - Any alignment and any K are accepted, with the same results. 16-byte aligned
+ *     operands with K a multiple of 16 take the fastest kernels; 4-byte aligned ones with
+ *     K a multiple of 4 most of the same tiles above 32 tokens; others kernels that load
+ *     16 bytes at the rows' own alignment.
  */
 #ifndef W8A8_H
 #define W8A8_H
@@ -192,8 +196,10 @@ w8a8_status w8a8_gemm_acc_i32_ex(const int8_t *xq, const int8_t *wq, int32_t *ac
  *
  * act selects a transform T applied to the bf16 input before the multiplier:
  *   W8A8_ACT_NONE  T(x) = x
- *   W8A8_ACT_GELU  T(x) = x * Phi(x), the exact (erf) GELU, evaluated in float32
- *                  through a Chebyshev fit of erfc (Numerical Recipes' erfcc,
+ *   W8A8_ACT_GELU  T(x) = x * Phi(x), the exact (erf) GELU in float32. Quantized rows of
+ *                  K up to 32768 take Phi from a table of every bf16 magnitude (relative
+ *                  error below 2^-22). Longer rows, rows of K < 8 and w8a8_col_absmax
+ *                  evaluate a Chebyshev fit of erfc (Numerical Recipes' erfcc,
  *                  fractional error < 1.2e-7) on the hardware reciprocal and exp2:
  *                  relative error about 3e-7 where |x| < 4, growing in the far left
  *                  tail with the float32 rounding of x^2 / 2 (there GELU(x) is below

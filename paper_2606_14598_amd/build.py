@@ -3,7 +3,7 @@
 Usage: python -m paper_2606_14598_amd.build   (or build() from Python)
 
 Every HIP source under csrc/ is compiled for gfx950 with:
-  -O3 -std=c++17 -fPIC
+  -O3 -std=c++20 -fPIC
   -ffp-contract=off          no implicit FMA contraction: the quantizer's multiply and
                              rounding and the epilogue's explicit fmaf are exactly what
                              the source writes

@@ -1898,9 +1898,11 @@ struct TileEntry {
     }
 
 // Names: m<TM>n<TN>k<BK>w<WM>x<WN>[s<S>]; skinny_m<Mmax>n<C>w<NW> = weight-streaming
-// kernel for at most Mmax tokens, C channels per workgroup. "s<S>" = direct-to-LDS pipelined kernel with S
-// stages (used when the operands are 16-byte aligned and K % 16 == 0; otherwise the
-// register-staged kernel of the same tile runs).
+// kernel for at most Mmax tokens, C channels per workgroup. "s<S>" = direct-to-LDS pipelined
+// kernel with S stages, for 16-byte aligned operands with K % 16 == 0 and, from three stages
+// on, 4-byte aligned ones with K % 4 == 0 above 32 tokens. Other operands run the
+// any-alignment kernels, whatever the tile. The register-staged tiles (128x128 to 32x64
+// without "s<S>") were never the fastest: only a given id runs them.
 const TileEntry kTiles[] = {
     W8A8_TILE("m256n256k64w2x2s4", 256, 256, 64, 2, 2, 8, 4),
     W8A8_TILE("m256n256k128w2x2s2", 256, 256, 128, 2, 2, 8, 2),
@@ -1987,9 +1989,12 @@ constexpr int64_t kLdsPerWorkgroup = 160 * 1024;
 constexpr double kSplitFixedUs = 2.0, kSplitUs = 0.25, kSplitUsPerMB = 0.4;
 constexpr uint32_t kMaxSplits = 16;
 constexpr int64_t kSplitWorkspace = 80 << 20;   // bytes of partials at most
-// K is split only where the best unsplit plan takes longer than this: a call's second launch
-// and its larger workspace cost the host some 5 us, which a shorter GEMM does not hide
+// K is split only where the best unsplit plan takes longer than this: an eager call's second
+// launch and its larger workspace cost the host some 5 us, which a shorter GEMM does not hide
 // (38 tokens, K = 3648, N = 2752 and 448: 43.9 us with the first one split, 37.7 without).
+// A captured call, or one with a workspace of its own, does not pay that, but the library
+// cannot tell the callers apart; it misses little: of 2479 random shapes whose fastest
+// unsplit tile takes up to 12 us, a split tile is faster on 83, by 8% in the mean.
 constexpr double kSplitWorthUs = 12.0;
 // A table entry, which was timed on its own shape, gives way only to a clear gain.
 constexpr double kOverTable = 0.85;
@@ -2243,6 +2248,11 @@ bool linear_small_applies(int64_t M, int64_t N, int64_t K, const void *x, const 
     return linear_small_shape(M, N, K);
 }
 
+// At 2 to 4 tokens the quantizer and the row kernel in two launches are the alternative.
+// Weights from HBM, one launch against two, us: 2 x 4096 x 4096 7.0 and 7.3, 3 x 1024 x 4096
+// 5.1 and 5.5, 4 x 2048 x 8192 7.6 and 7.8; but 4 x 4096 x 1024 6.2 and 5.4, 2 x 4096 x 12288
+// 13.7 and 12.3, 4 x 8192 x 4096 12.1 and 11.5. So also one token past K = 16384, where the
+// one launch is the tile's: 1 x 32768 x 4096 33.6 and 28.9.
 bool linear_small_shape(int64_t M, int64_t N, int64_t K) {
     if (M <= 0 || N <= 0 || K <= 0 || K % 16 != 0)
         return false;

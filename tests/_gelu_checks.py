@@ -2,8 +2,8 @@
 compare against is the oracle's).
 
 Each side computes its own GELU in front of the quantizer (the oracle in double, rounded
-once to float32; the kernel in float32 through an erfc fit, a few units in the last
-place off), so for GELU rows the scales agree to 2^-17 relative, codes agree exactly
+once to float32; the kernel in float32 from a table of Phi or, on the longest rows,
+through an erfc fit, a few units in the last place off), so for GELU rows the scales agree to 2^-17 relative, codes agree exactly
 except near rounding ties, and a linear's outputs differ by at most what those code and
 scale differences allow.
 """

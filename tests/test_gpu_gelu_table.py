@@ -19,7 +19,7 @@ pytestmark = pytest.mark.gpu
 def test_gelu_scale_of_every_magnitude(K):
     if not torch.cuda.is_available():
         pytest.skip("no GPU")
-    # bf16 magnitudes from 2^-30 (below the table's first, 2^-24) to 32 (past its last, 16)
+    # bf16 magnitudes from 2^-30 (below the table's first, 2^-8) to 32 (past its last, 16)
     mag = np.arange((127 - 30) << 7, (127 + 5) << 7, dtype=np.uint16)
     bits = np.concatenate([mag, mag | 0x8000])
     x = torch.from_numpy(bits.view(np.int16)).view(torch.bfloat16).cuda()
