@@ -847,20 +847,21 @@ def paper_shapes(args):
                              device=dev)
             ops = gemm_ops(M, N, K)
             it = 20 if ops < 5e14 else 5
-            ids = {"plan": -1, "tuned": w8a8.select_tile(M, N, K),
-                   "default": w8a8.default_tile(M, N, K), "fixed": FIXED_TILE}
+            ids = {"tuned": w8a8.select_tile(M, N, K), "default": w8a8.default_tile(M, N, K),
+                   "fixed": FIXED_TILE, "plan": -1}
+            names = {a: w8a8.plan_name(M, N, K) if i < 0 else w8a8.tile_name(i)
+                     for a, i in ids.items()}
             gws = torch.empty(max(1, *(w8a8.gemm_workspace_bytes(M, N, K, i)
                                        for i in ids.values())), dtype=torch.uint8, device=dev)
             t = {}
             for arm, tid in ids.items():
-                same = [a for a in t if ids[a] == tid]
+                same = [a for a in t if names[a] == names[arm]]
                 t[arm] = t[same[0]] if same else graph_ms(
                     lambda: w8a8.gemm(xq, sx, wq, sw, bd, tile=tid, out=y, workspace=gws), it)
             t["linear"] = graph_ms(lambda: w8a8.linear(xd, wq, sw, bd, out=y, workspace=ws), it)
             t["bf16"] = graph_ms(lambda: F.linear(xd, wd, bd), it)
             rec = {"what": "paper_shape", "shape": name, "M": M, "N": N, "K": K,
-                   "tiles": {a: w8a8.plan_name(M, N, K) if i < 0 else w8a8.tile_name(i)
-                             for a, i in ids.items()},
+                   "tiles": names,
                    "us": {a: round(v * 1e3, 2) for a, v in t.items()},
                    "tops": {a: round(ops / t[a] / 1e9, 1) for a in ("plan", "linear", "bf16")},
                    "gemm_pct_int8_peak": round(100 * ops / t["plan"] / 1e9 / PEAK_INT8_TOPS, 2),
