@@ -94,7 +94,8 @@ size_t w8a8_gemm_workspace_least_bytes(int64_t M, int64_t N, int64_t K);
 
 /* Workspace of w8a8_gemm_ex with a given tile id (-1: the library's choice). Tiles that
  * split K among several workgroups per output tile keep int32 partial products
- * [splits][M][N] there; the others need none (0). */
+ * [splits][M][N] there; the others need none (0), and no tile does where K sends the
+ * operands to the any-alignment kernels (K % 4 != 0, or K % 16 != 0 up to 32 tokens). */
 size_t w8a8_gemm_workspace_bytes_ex(int64_t M, int64_t N, int64_t K, int tile_id);
 
 /* The whole quantized linear: per-token quantization of x into the workspace, then the
