@@ -1996,6 +1996,11 @@ constexpr int64_t kSplitWorkspace = 80 << 20;   // bytes of partials at most
 // cannot tell the callers apart; it misses little: of 2479 random shapes whose fastest
 // unsplit tile takes up to 12 us, a split tile is faster on 83, by 8% in the mean.
 constexpr double kSplitWorthUs = 12.0;
+// A split has to be predicted this much faster than the best unsplit plan: below, the
+// predictions decide by chance, and a split costs a launch and a workspace (160 x 8192 x 4096
+// 20.2 us split in four, 18.8 unsplit; 333 x 8192 x 4096 26.9 and 25.9). On 3800 random
+// shapes the mean distance from the fastest tile stays within 0.1%.
+constexpr double kSplitGain = 0.95;
 // A table entry, which was timed on its own shape, gives way only to a clear gain.
 constexpr double kOverTable = 0.85;
 
@@ -2135,10 +2140,10 @@ static bool stream_fits(const TileInfo &t, int64_t M, int64_t K) {
 // What runs a shape by default. Up to 16 tokens, and where K sends the operands to the
 // any-alignment kernels, the selected tile. Above, the least predicted time over the tiles,
 // each unsplit and with K split in as many ways as fit one round of workgroups; a table
-// entry stays unless the prediction beats its own clearly. On 900 random shapes (tune.py
+// entry stays unless the prediction beats its own clearly. On 1100 random shapes (tune.py
 // --random, other ones than the costs were fitted to; weights from HBM) the choice is within
-// 0.6% of the fastest tile for 17 to 32 tokens (geometric mean), 0.8% up to 64, 1.2% up to
-// 128 and 2.0% above; the fallback tile 16, 19, 31 and 10%: long K on few output tiles left
+// 1.1% of the fastest tile up to 128 tokens (geometric mean) and 2.2% above; the fallback tile
+// within 16% up to 32 tokens, 21 up to 64, 32 up to 128 and 13 above: long K on few output tiles left
 // most CUs idle (512 x 4608 x 53248: 162.7 us split in two, 138.8 in seven on 252
 // workgroups), and tiles without a deep ring were taken for small outputs (640 x 1024 x
 // 4096: 20.7 against 11.0 us). The streaming tiles' costs hold for the kernels of their
@@ -2186,6 +2191,7 @@ static GemmPlan compute_plan(int64_t M, int64_t N, int64_t K) {
         const uint32_t tiles = tiles_of(t);
         consider(id, 1, plan_cost_us(id, tiles, 1, mn, k));
     }
+    limit = std::min(limit, kSplitGain * unsplit);
     for (int id = 0; id < kNumTiles && unsplit > kSplitWorthUs; ++id) {
         const TileInfo &t = kTiles[id].info;
         if (t.base >= 0 || !t.splittable || !(kTileCost[id].d > 0.0) || !(aligned || t.dword))
